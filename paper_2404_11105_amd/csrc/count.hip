@@ -39,6 +39,14 @@ constexpr uint32_t kIdlePolls = 1u << 13;  // polls a waiting wave makes for don
 constexpr uint32_t kMaxWaiters = 512;      // waves that wait for donated work; the others leave
 constexpr uint32_t kDonateAfter = 256;     // windows a task runs before it may donate
 constexpr uint32_t kComplete = 0x80000000u;
+// Base lists at least this long are scanned by the whole wave on their own
+// (wide_scan).  Measured at 32 / 64 / 128: unreduced motifs on R-MAT 16 192 /
+// 174 / 181 ms, 96 plans on R-MAT 22 414 / 393 / 392 ms: one tile per scan is
+// the shortest list that pays for reading the parent's probes.
+#ifndef XM_WIDE_MIN
+#define XM_WIDE_MIN 64
+#endif
+constexpr uint32_t kWideMin = XM_WIDE_MIN;
 
 __device__ __forceinline__ uint32_t uni(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
 __device__ __forceinline__ uint32_t lane_id() {
@@ -79,7 +87,8 @@ __device__ __forceinline__ uint32_t scan_max(uint32_t v) {
 }
 
 // Sorted-list membership: branchless search for the last element <= x.
-__device__ __forceinline__ bool contains(const uint32_t* __restrict__ a, uint32_t len, uint32_t x) {
+template <class P>
+__device__ __forceinline__ bool contains(P a, uint32_t len, uint32_t x) {
     if (len == 0) return false;
     uint32_t base = 0, n = len;
     while (n > 1) {
@@ -112,8 +121,12 @@ __device__ __forceinline__ const uint32_t* probe_ref(const DevGraph& g, uint32_t
     return adj_of(g, dir) + o;
 }
 
-__device__ __forceinline__ const uint32_t* join_ptr(uint32_t lo, uint32_t hi) {
-    return reinterpret_cast<const uint32_t*>(((uint64_t)hi << 32) | lo);
+// A list or row address put together from two words.  The address space is
+// stated: the compiler cannot infer it from an integer, and a flat load
+// would also go through the LDS path and its wait counter.
+typedef const __attribute__((address_space(1))) uint32_t* gptr;
+__device__ __forceinline__ gptr join_ptr(uint32_t lo, uint32_t hi) {
+    return reinterpret_cast<gptr>(((uint64_t)hi << 32) | lo);
 }
 
 // Any address that may be read (a lane with nothing to probe reads it and
@@ -247,7 +260,7 @@ __device__ __forceinline__ uint32_t level1_len(const DevGraph& g, const PlanDesc
 }
 
 // Number of elements <= x in the sorted list a[0, n).
-__device__ __forceinline__ uint32_t count_le(const uint32_t* __restrict__ a, uint32_t n, uint32_t x) {
+__device__ __forceinline__ uint32_t count_le(const uint32_t* a, uint32_t n, uint32_t x) {
     uint32_t lo = 0;
     while (n > 0) {
         const uint32_t h = n >> 1;
@@ -287,7 +300,7 @@ __device__ __forceinline__ void sym_trim(const Lds& s, uint32_t gt, uint32_t lt,
 // list and writes the probes (the other constraint lists, long ones as their
 // dense rows) into the parent's probe slots.  Returns the base length.
 template <bool IS_SIG>
-__device__ uint32_t phase_a(Ctx& C, const LK& D, uint32_t lv, uint32_t p, bool pv, bool walk) {
+__device__ __forceinline__ uint32_t phase_a(Ctx& C, const LK& D, uint32_t lv, uint32_t p, bool pv, bool walk) {
     const KArgs& a = *C.a;
     const DevGraph& g = a.g;
     const uint32_t lane = C.lane;
@@ -427,8 +440,8 @@ __device__ __forceinline__ void tile_parents(const Lds& s, uint32_t lane, uint32
 // Two sorted-list searches per lane (one per element), both loads of a step
 // issued together.  A lane without a search passes n = 0 and a readable
 // pointer (its value is ignored).
-__device__ __forceinline__ void search2(const uint32_t* __restrict__ A, uint32_t na, uint32_t xa, bool& fa,
-                                        const uint32_t* __restrict__ B, uint32_t nb, uint32_t xb, bool& fb) {
+__device__ __forceinline__ void search2(gptr A, uint32_t na, uint32_t xa, bool& fa, gptr B, uint32_t nb,
+                                        uint32_t xb, bool& fb) {
     uint32_t ba = 0, bb = 0, ra = na, rb = nb;
     while (__ballot(ra > 1 || rb > 1)) {
         const uint32_t ha = ra >> 1, hb = rb >> 1;
@@ -445,7 +458,7 @@ __device__ __forceinline__ void search2(const uint32_t* __restrict__ A, uint32_t
 
 // Membership of x in probe (ptr, len) for one lane: a dense-row bit or a
 // sorted-list search (no test when len is kSkip: returns true).
-__device__ __forceinline__ bool probe_one(const uint32_t* ptr, uint32_t len, uint32_t x) {
+__device__ __forceinline__ bool probe_one(gptr ptr, uint32_t len, uint32_t x) {
     if (len == kSkip) return true;
     if (len == kRowLen) return (ptr[x >> 5] >> (x & 31u)) & 1u;
     return contains(ptr, len, x);
@@ -471,11 +484,11 @@ __device__ __forceinline__ void check_pair(const Ctx& C, const LK& D, uint32_t i
         oka = oka && (da & 15u) >= D.dmin_out && (da >> 4) >= D.dmin_in;
         okb = okb && (db & 15u) >= D.dmin_out && (db >> 4) >= D.dmin_in;
     }
-    const uint32_t* safe = safe_ptr(g);
+    const gptr safe = (gptr)safe_ptr(g);
     for (uint32_t k = 0; k < ns; k++) {
         const uint32_t lA = C.s.slot_len[k * 64 + ja], lB = C.s.slot_len[k * 64 + jb];
-        const uint32_t* pA = join_ptr(C.s.slot_lo[k * 64 + ja], C.s.slot_hi[k * 64 + ja]);
-        const uint32_t* pB = join_ptr(C.s.slot_lo[k * 64 + jb], C.s.slot_hi[k * 64 + jb]);
+        const gptr pA = join_ptr(C.s.slot_lo[k * 64 + ja], C.s.slot_hi[k * 64 + ja]);
+        const gptr pB = join_ptr(C.s.slot_lo[k * 64 + jb], C.s.slot_hi[k * 64 + jb]);
         const bool rA = oka && lA == kRowLen, rB = okb && lB == kRowLen;
         if (__ballot(rA || rB)) {
             const uint32_t wa = (rA ? pA : safe)[rA ? (xa >> 5) : 0u];
@@ -496,6 +509,112 @@ __device__ __forceinline__ void check_pair(const Ctx& C, const LK& D, uint32_t i
     }
 }
 
+// One step of a wide scan: U tiles of the base list from element i0 on, tested
+// against the parent's probes.  Everything but the element is the same for all
+// lanes: base, rows and lists sit in scalar registers.
+template <int U, class F>
+__device__ __forceinline__ void wide_step(const Ctx& C, const LK& D, uint32_t inj, uint32_t lv, uint32_t j,
+                                          gptr base, uint32_t len, uint32_t i0, uint32_t nrow, gptr r0, gptr r1,
+                                          uint32_t rest, F&& emit) {
+    const DevGraph& g = C.a->g;
+    uint32_t x[U];
+    bool ok[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+        const uint32_t i = i0 + (uint32_t)u * 64u + C.lane;
+        ok[u] = i < len;
+        x[u] = base[ok[u] ? i : i0];
+    }
+    for (uint32_t l = 0; l < lv; l++)
+        if ((inj >> l) & 1u) {
+            const uint32_t b = uni(C.s.bound[l * 64 + j]);
+#pragma unroll
+            for (int u = 0; u < U; u++) ok[u] = ok[u] && x[u] != b;
+        }
+    if (D.deg_check) {
+        uint32_t d[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) d[u] = g.degc[ok[u] ? x[u] : 0u];
+#pragma unroll
+        for (int u = 0; u < U; u++) ok[u] = ok[u] && (d[u] & 15u) >= D.dmin_out && (d[u] >> 4) >= D.dmin_in;
+    }
+    // a lane that is out already reads the row's first word
+    auto row_test = [&](gptr r) {
+        uint32_t w[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) w[u] = r[ok[u] ? x[u] >> 5 : 0u];
+#pragma unroll
+        for (int u = 0; u < U; u++) ok[u] = ok[u] && __builtin_amdgcn_ubfe(w[u], x[u], 1u) != 0;
+    };
+    if (nrow > 0) row_test(r0);
+    if (nrow > 1) row_test(r1);
+    for (uint32_t m = rest; m; m &= m - 1) {
+        const uint32_t k = (uint32_t)__builtin_ctz(m);
+        const uint32_t n = uni(C.s.slot_len[k * 64 + j]);
+        const gptr p = join_ptr(uni(C.s.slot_lo[k * 64 + j]), uni(C.s.slot_hi[k * 64 + j]));
+        if (n == kRowLen) {
+            row_test(p);
+            continue;
+        }
+        // a sorted list of the same length for every lane: the searches of all
+        // tiles halve together
+        uint32_t b[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) b[u] = 0;
+        for (uint32_t r = n; r > 1;) {
+            const uint32_t h = r >> 1;
+            uint32_t v[U];
+#pragma unroll
+            for (int u = 0; u < U; u++) v[u] = p[b[u] + h];
+#pragma unroll
+            for (int u = 0; u < U; u++) b[u] = v[u] <= x[u] ? b[u] + h : b[u];
+            r -= h;
+        }
+        uint32_t v[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) v[u] = p[b[u]];
+#pragma unroll
+        for (int u = 0; u < U; u++) ok[u] = ok[u] && v[u] == x[u];
+    }
+#pragma unroll
+    for (int u = 0; u < U; u++) emit(x[u], ok[u]);
+}
+
+// Candidate tests of one window parent j whose base list is long, by the whole
+// wave: the elements base[0, len) in order, 64 at a time; emit(x, ok) is called
+// for each tile.  A flattened tile pays for its generality (which parent owns
+// the element, its base and probe slots from LDS: ~70 VALU instructions per 64
+// elements); here these are uniform and a tile against one row takes ~10.
+// Measured, flattened only and with this: TT4 + pendant on R-MAT 18 313 and
+// 134 ms, C5 + chord on R-MAT 20 (1/256 of the roots) 229 and 97 ms, 96 plans on
+// R-MAT 22 614 and 385 ms, four unreduced motifs on R-MAT 16 162 and 157 ms (bound
+// by the row gathers either way: one TD clock per 32-byte sector a load touches).
+template <class F>
+__device__ __forceinline__ void wide_scan(const Ctx& C, const LK& D, uint32_t inj, uint32_t lv, uint32_t ns,
+                                          uint32_t j, gptr base, uint32_t len, F&& emit) {
+    gptr r0 = base, r1 = base;
+    uint32_t nrow = 0, rest = 0;
+    for (uint32_t k = 0; k < ns; k++) {
+        const uint32_t l = uni(C.s.slot_len[k * 64 + j]);
+        if (l == kSkip) continue;
+        if (l == 0) return;  // an empty list holds nothing
+        if (l == kRowLen && nrow < 2) {
+            const gptr p = join_ptr(uni(C.s.slot_lo[k * 64 + j]), uni(C.s.slot_hi[k * 64 + j]));
+            if (nrow == 0) r0 = p;
+            else r1 = p;
+            nrow++;
+        } else {
+            rest |= 1u << k;
+        }
+    }
+    uint32_t i0 = 0;
+    for (; i0 + 128 < len; i0 += 256) wide_step<4>(C, D, inj, lv, j, base, len, i0, nrow, r0, r1, rest, emit);
+    for (; i0 < len; i0 += 128) {
+        if (i0 + 64 < len) wide_step<2>(C, D, inj, lv, j, base, len, i0, nrow, r0, r1, rest, emit);
+        else wide_step<1>(C, D, inj, lv, j, base, len, i0, nrow, r0, r1, rest, emit);
+    }
+}
+
 // Whether bound node y of this lane's partial match lies in the lane's base
 // list and passes all its probes: then a flattened pass without injectivity
 // counted it once.
@@ -510,9 +629,18 @@ __device__ __forceinline__ bool bound_in_set(const Ctx& C, uint32_t ns, uint32_t
     return true;
 }
 
+// Elements of window parent j's long base list that pass all its probes (no
+// injectivity: leaf passes settle that per partial match).
+__device__ __forceinline__ uint32_t wide_count(const Ctx& C, const LK& D, uint32_t lv, uint32_t ns, uint32_t j) {
+    uint32_t cnt = 0;
+    wide_scan(C, D, 0u, lv, ns, j, join_ptr(uni(C.s.base_lo[j]), uni(C.s.base_hi[j])), uni(C.s.base_len[j]),
+              [&](uint32_t, bool ok) { cnt += (uint32_t)__popcll(__ballot(ok)); });
+    return cnt;
+}
+
 // Expand one window of level lv from the parents in level lv-1.  Returns the
 // number of children written to level lv's buffer.
-__device__ uint32_t expand(Ctx& C, uint32_t lv) {
+__device__ __forceinline__ uint32_t expand(Ctx& C, uint32_t lv) {
     const KArgs& a = *C.a;
     const LK D = load_lk(C.P->lvl[lv], a);
     const uint32_t lane = C.lane;
@@ -547,39 +675,69 @@ __device__ uint32_t expand(Ctx& C, uint32_t lv) {
     const uint32_t start = incl - len;
     wave_sync();
     Lvl Fo = lvl_arrays(C.scr, cap, lv);
-    uint32_t nout = 0, carry = 0;
+    uint32_t nout = 0;
     const uint32_t ns = n_slots(D);
-    // two tiles per step: survivors of tile a are written before those of
-    // tile b, so each parent's children stay contiguous and in order
-    for (uint32_t t0 = 0; t0 < T; t0 += 128) {
-        const uint32_t ga = t0 + lane, gb = t0 + 64 + lane;
-        uint32_t ja, jb;
-        tile_parents(C.s, lane, t0, start, owns, carry, ja, jb);
-        bool oka = ga < T, okb = gb < T;
-        uint32_t xa = 0, xb = 0;
-        const uint32_t la = ga - (ja ? C.s.incl[ja - 1] : 0u) + (ja == 0 ? pofs : 0u);
-        const uint32_t lb = gb - (jb ? C.s.incl[jb - 1] : 0u) + (jb == 0 ? pofs : 0u);
-        oka = oka && la < C.s.base_len[ja];
-        okb = okb && lb < C.s.base_len[jb];
-        if (oka) xa = base_elem(C, ja, la);
-        if (okb) xb = base_elem(C, jb, lb);
-        check_pair(C, D, D.inj, lv, ns, ja, xa, oka, jb, xb, okb);
-        const uint64_t ma = __ballot(oka);
-        if (oka) {
-            const uint32_t pos = nout + rank_below(ma);
-            Fo.node[pos] = xa;
-            Fo.parent[pos] = cur + ja;
-            if (seg) atomicAdd(&C.s.segcnt[ja], 1u);
+    // parents with a long base are scanned one by one, the runs between them
+    // flattened; children are written in parent order either way
+    const uint64_t wide = __ballot(lane < np && len >= kWideMin);
+    for (uint32_t j0 = 0; j0 < np;) {
+        const uint64_t ahead = wide >> j0;
+        if (ahead & 1u) {
+            const uint32_t before = nout;
+            const uint32_t off = j0 == 0 ? pofs : 0u;
+            const gptr base = join_ptr(uni(C.s.base_lo[j0]), uni(C.s.base_hi[j0])) + off;
+            const uint32_t n = uni(__shfl(len, (int)j0, 64));
+            wide_scan(C, D, D.inj, lv, ns, j0, base, n, [&](uint32_t x, bool ok) {
+                const uint64_t m = __ballot(ok);
+                if (ok) {
+                    const uint32_t pos = nout + rank_below(m);
+                    Fo.node[pos] = x;
+                    Fo.parent[pos] = cur + j0;
+                }
+                nout += (uint32_t)__popcll(m);
+            });
+            if (seg && lane == 0) C.s.segcnt[j0] = nout - before;
+            j0++;
+            continue;
         }
-        nout += (uint32_t)__popcll(ma);
-        const uint64_t mb = __ballot(okb);
-        if (okb) {
-            const uint32_t pos = nout + rank_below(mb);
-            Fo.node[pos] = xb;
-            Fo.parent[pos] = cur + jb;
-            if (seg) atomicAdd(&C.s.segcnt[jb], 1u);
+        // the run of short parents [j0, j1): elements [e0, e1)
+        uint32_t j1 = ahead ? j0 + (uint32_t)__builtin_ctzll(ahead) : np;
+        j1 = j1 < np ? j1 : np;
+        const uint32_t e0 = uni(__shfl(start, (int)j0, 64)), e1 = uni(__shfl(incl, (int)j1 - 1, 64));
+        uint32_t carry = j0;
+        // two tiles per step: survivors of tile a are written before those of
+        // tile b, so each parent's children stay contiguous and in order
+        for (uint32_t t0 = e0; t0 < e1; t0 += 128) {
+            const uint32_t ga = t0 + lane, gb = t0 + 64 + lane;
+            uint32_t ja, jb;
+            tile_parents(C.s, lane, t0, start, owns, carry, ja, jb);
+            bool oka = ga < e1, okb = gb < e1;
+            uint32_t xa = 0, xb = 0;
+            const uint32_t la = ga - (ja ? C.s.incl[ja - 1] : 0u) + (ja == 0 ? pofs : 0u);
+            const uint32_t lb = gb - (jb ? C.s.incl[jb - 1] : 0u) + (jb == 0 ? pofs : 0u);
+            oka = oka && la < C.s.base_len[ja];
+            okb = okb && lb < C.s.base_len[jb];
+            if (oka) xa = base_elem(C, ja, la);
+            if (okb) xb = base_elem(C, jb, lb);
+            check_pair(C, D, D.inj, lv, ns, ja, xa, oka, jb, xb, okb);
+            const uint64_t ma = __ballot(oka);
+            if (oka) {
+                const uint32_t pos = nout + rank_below(ma);
+                Fo.node[pos] = xa;
+                Fo.parent[pos] = cur + ja;
+                if (seg) atomicAdd(&C.s.segcnt[ja], 1u);
+            }
+            nout += (uint32_t)__popcll(ma);
+            const uint64_t mb = __ballot(okb);
+            if (okb) {
+                const uint32_t pos = nout + rank_below(mb);
+                Fo.node[pos] = xb;
+                Fo.parent[pos] = cur + jb;
+                if (seg) atomicAdd(&C.s.segcnt[jb], 1u);
+            }
+            nout += (uint32_t)__popcll(mb);
         }
-        nout += (uint32_t)__popcll(mb);
+        j0 = j1;
     }
     wave_sync();
     if (seg) {
@@ -618,8 +776,7 @@ __device__ uint32_t expand(Ctx& C, uint32_t lv) {
 // chunk, and the chunk with the smaller maximum advances (both on a tie), so
 // every matching pair is seen exactly once.  Reads are coalesced and no
 // dependent global search is needed (merge path for balanced list sizes).
-__device__ uint32_t merge_count(const Lds& s, const uint32_t* __restrict__ A, uint32_t na,
-                                const uint32_t* __restrict__ B, uint32_t nb, uint32_t inj, uint32_t nbound,
+__device__ uint32_t merge_count(const Lds& s, gptr A, uint32_t na, gptr B, uint32_t nb, uint32_t inj, uint32_t nbound,
                                 uint32_t j, uint32_t lane) {
     constexpr uint32_t U = kMergeChunk / 64;
     uint32_t ia = 0, ib = 0, cnt = 0;
@@ -680,7 +837,7 @@ __device__ __forceinline__ uint32_t own_count(uint64_t ballot, uint32_t start, u
 // length minus bound hits when M has a single constraint list), then the
 // inclusion-exclusion terms over set partitions of the leaves are summed in
 // 128-bit integers.  The 64 lanes hold the 64 partial matches [w0, w0 + 64).
-__device__ void leaf_masks(Ctx& C, uint32_t nb, uint32_t p, bool pv) {
+__device__ __forceinline__ void leaf_masks(Ctx& C, uint32_t nb, uint32_t p, bool pv) {
     const KArgs& a = *C.a;
     const PlanDesc* P = C.P;
     const uint32_t lane = C.lane;
@@ -701,8 +858,11 @@ __device__ void leaf_masks(Ctx& C, uint32_t nb, uint32_t p, bool pv) {
                     if (((K.inj >> b) & 1u) && contains(L, l, C.s.bound[b * 64 + lane])) h -= 1;
             }
         } else {
-            const uint32_t len = phase_a<true>(C, K, nb, p, pv, false);
+            uint32_t len = phase_a<true>(C, K, nb, p, pv, false);
             const uint32_t ns = n_slots(K);
+            // long base lists are scanned one by one after the flattened pass
+            uint64_t wide = __ballot(len >= kWideMin);
+            if (len >= kWideMin) len = 0;
             const uint32_t incl = scan_incl(len, lane);
             C.s.incl[lane] = incl;
             const uint32_t T = uni(__shfl(incl, 63, 64));
@@ -725,6 +885,11 @@ __device__ void leaf_masks(Ctx& C, uint32_t nb, uint32_t p, bool pv) {
                 check_pair(C, K, 0u, nb, ns, ja, xa, oka, jb, xb, okb);
                 const uint64_t ba = __ballot(oka), bb = __ballot(okb);
                 if (owns) h += own_count(ba, start, len, t0) + own_count(bb, start, len, t0 + 64);
+            }
+            for (; wide; wide &= wide - 1) {
+                const uint32_t j = (uint32_t)__builtin_ctzll(wide);
+                const uint32_t cnt = wide_count(C, K, nb, ns, j);
+                h = lane == j ? cnt : h;
             }
             // the bound nodes the set may not contain were counted if present
             if (pv)
@@ -784,7 +949,7 @@ __device__ __forceinline__ void write_rows(const Ctx& C, uint32_t nb, uint64_t m
 
 // Count the leaf group for every partial match in level `lv` (= e - 1).
 template <bool NONLIN>
-__device__ void count_leaves(Ctx& C, uint32_t lv, uint32_t nprefix) {
+__device__ __forceinline__ void count_leaves(Ctx& C, uint32_t lv, uint32_t nprefix) {
     const KArgs& a = *C.a;
     const PlanDesc* P = C.P;
     const uint32_t lane = C.lane;
@@ -864,7 +1029,9 @@ __device__ void count_leaves(Ctx& C, uint32_t lv, uint32_t nprefix) {
                 }
             }
             uint64_t bigmask = __ballot(big);
-            if (big) len = 0;
+            // other long base lists are scanned one by one (listing stays flattened)
+            uint64_t wide = __ballot(len >= kWideMin && !big && !listing);
+            if (big || (len >= kWideMin && !listing)) len = 0;
             (void)nsig;
             const uint32_t incl = scan_incl(len, lane);
             C.s.incl[lane] = incl;
@@ -893,6 +1060,8 @@ __device__ void count_leaves(Ctx& C, uint32_t lv, uint32_t nprefix) {
                 lin += (unsigned long long)(__popcll(ma) + __popcll(mb));
                 if (listing) write_rows(C, nb, ma, mb, ja, xa, oka, jb, xb, okb);
             }
+            for (; wide; wide &= wide - 1)
+                lin += wide_count(C, S, nb, ns, (uint32_t)__builtin_ctzll(wide));
             // bound nodes the leaf may not take were counted if they are in the set
             for (uint32_t b = 0; b < nb && !listing; b++) {
                 if (!((S.inj >> b) & 1u)) continue;
@@ -910,8 +1079,8 @@ __device__ void count_leaves(Ctx& C, uint32_t lv, uint32_t nprefix) {
                     if (C.s.slot_len[c * 64 + j] != kSkip) pc = c;
                 pc = uni(pc);
                 const uint32_t plen = uni(C.s.slot_len[pc * 64 + j]);
-                const uint32_t* A = join_ptr(uni(C.s.base_lo[j]), uni(C.s.base_hi[j]));
-                const uint32_t* B = join_ptr(uni(C.s.slot_lo[pc * 64 + j]), uni(C.s.slot_hi[pc * 64 + j]));
+                const gptr A = join_ptr(uni(C.s.base_lo[j]), uni(C.s.base_hi[j]));
+                const gptr B = join_ptr(uni(C.s.slot_lo[pc * 64 + j]), uni(C.s.slot_hi[pc * 64 + j]));
                 lin += merge_count(C.s, A, blen, B, plen, S.inj, nb, j, lane);
             }
         }
@@ -920,7 +1089,7 @@ __device__ void count_leaves(Ctx& C, uint32_t lv, uint32_t nprefix) {
     }
 }
 
-__device__ void flush(Ctx& C) {
+__device__ __forceinline__ void flush(Ctx& C) {
     unsigned long long lo = C.acc_lo, hi = C.acc_hi;
     bool ovf = C.ovf;
     // wave reduction of 128-bit partials
@@ -947,7 +1116,7 @@ __device__ void flush(Ctx& C) {
 // prefix phi(v_0..v_{l-1}); the donor drops them from its window.  A donated
 // task is explored from level l by another wave.  Slots are reserved with a
 // CAS on the tail (never past the capacity) and published with a ready flag.
-__device__ void maybe_donate(Ctx& C, uint32_t start, uint32_t lv) {
+__device__ __forceinline__ void maybe_donate(Ctx& C, uint32_t start, uint32_t lv) {
     const KArgs& a = *C.a;
     uint32_t* st = C.s.st;
     uint32_t idle = 0;
@@ -997,7 +1166,7 @@ __device__ void maybe_donate(Ctx& C, uint32_t start, uint32_t lv) {
 // Depth-first exploration of the n0 partial matches held in level start-1
 // (start = 1: roots in level 0).
 template <bool NONLIN>
-__device__ void explore(Ctx& C, uint32_t n0, uint32_t start) {
+__device__ __forceinline__ void explore(Ctx& C, uint32_t n0, uint32_t start) {
     const uint32_t e = C.P->e;
     uint32_t* st = C.s.st;
     if (e == 1) {

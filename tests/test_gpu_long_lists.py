@@ -1,0 +1,70 @@
+"""Base lists scanned one by one by a whole wave: list lengths at the edges of
+its steps (one, two and four tiles of 64 elements, and remainders), with dense
+rows, with sorted-list searches and with both among one parent's probes.
+Counts are whole numbers and equal the oracle's."""
+import numpy as np
+import pytest
+
+import oracle
+import xmgen
+
+pytestmark = pytest.mark.gpu
+
+LENGTHS = [1, 31, 63, 64, 65, 127, 128, 129, 191, 192, 193, 255, 256, 257, 320, 321, 449, 512, 513]
+
+
+def lists_graph(seed=7, n=1301):
+    """Node i's out-list has LENGTHS[i] random nodes, node 40 + i's in-list
+    too, and arcs among the first 90 nodes close many small patterns."""
+    rng = np.random.default_rng(seed)
+    src, dst = [], []
+    for i, ln in enumerate(LENGTHS):
+        to = rng.choice(np.arange(90, n), ln, replace=False)
+        src += [np.full(ln, i), to]
+        dst += [to, np.full(ln, 40 + i)]
+    core = rng.random((90, 90)) < 0.3
+    u, v = np.nonzero(core)
+    extra = rng.integers(0, n, (2, 2000))
+    return xmgen.from_arcs(n, np.concatenate(src + [u, extra[0]]), np.concatenate(dst + [v, extra[1]]))
+
+
+@pytest.fixture(scope="module")
+def xa():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2404_11105_amd as xa
+    return xa
+
+
+@pytest.fixture(scope="module")
+def case():
+    g = lists_graph()
+    pats = [xmgen.named(p) for p in ("ffl", "c3", "bifan", "c4")]
+    return g, pats, [oracle.count(g, p) for p in pats]
+
+
+@pytest.mark.parametrize("rows", [dict(dense_rows=0), dict(row_min=32), dict(row_min=200)])
+@pytest.mark.parametrize("opts", [dict(), dict(cap=64, split=64), dict(cap=200, split=128, waves_per_cu=4)])
+def test_lists_at_step_edges(xa, case, rows, opts):
+    g, pats, want = case
+    print("[case]", rows, opts, flush=True)
+    G = xa.Graph(g, **rows)
+    for reduced in (True, False):
+        assert xa.count(G, [xa.Plan(p, reduced=reduced, graph=G) for p in pats], **opts) == want
+    sym = [xa.Plan(p, graph=G, symmetry=s) for p in pats for s in ("above", "below")]
+    assert xa.count(G, sym, **opts) == [w for w in want for _ in range(2)]
+
+
+@pytest.mark.parametrize("rows", [dict(dense_rows=0), dict(row_min=64)])
+def test_several_probes_per_parent(xa, rows):
+    """Four mutually joined vertices plus a leaf: up to three probes a test."""
+    rng = np.random.default_rng(3)
+    n = 400
+    u, v = np.nonzero(rng.random((n, n)) < 0.2)
+    g = xmgen.from_arcs(n, u, v)
+    pats = [xmgen.Pattern(4, ((0, 1), (0, 2), (0, 3), (1, 2), (1, 3), (2, 3))),
+            xmgen.Pattern(4, ((0, 1), (1, 0), (0, 2), (1, 2), (3, 0), (3, 1), (2, 3)))]
+    G = xa.Graph(g, **rows)
+    for reduced in (True, False):
+        assert xa.count(G, [xa.Plan(p, reduced=reduced, graph=G) for p in pats]) == [oracle.count(g, p) for p in pats]
