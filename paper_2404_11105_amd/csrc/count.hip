@@ -35,8 +35,8 @@ namespace xm {
 static_assert(sizeof(PlanDesc) % 4 == 0, "plan descriptors are copied in 32-bit words");
 
 constexpr uint32_t kSkip = 0xFFFFFFFFu;
-constexpr uint32_t kIdlePolls = 1u << 13;  // polls a waiting wave makes for donated work (at most ~28 us apart)
-constexpr uint32_t kMaxWaiters = 512;      // waves that wait for donated work; the others leave
+constexpr uint32_t kIdlePolls = 1u << 13;  // polls a waiting wave makes for donated work
+constexpr uint32_t kNapMax = 128;          // longest pause between two polls, in sleeps of 512 clocks (~27 us)
 constexpr uint32_t kDonateAfter = 256;     // windows a task runs before it may donate
 constexpr uint32_t kComplete = 0x80000000u;
 // Base lists at least this long are scanned by the whole wave on their own
@@ -658,17 +658,13 @@ __device__ __forceinline__ uint32_t expand(Ctx& C, uint32_t lv) {
     if (seg) C.s.segcnt[lane] = 0;
     const uint32_t cap = a.cap;
     uint32_t np = uni((uint32_t)__popcll(__ballot(pv && incl <= cap)));
-    uint32_t T;
     bool partial = false;
     if (np == 0) {
         // the first parent alone exceeds the buffer: take a slice of it
-        T = cap;
         partial = true;
         np = 1;
         if (lane == 0) incl = len = cap;
         C.s.incl[0] = cap;
-    } else {
-        T = uni(__shfl(incl, (int)np - 1, 64));
     }
     // lane j < np owns the elements [incl - len, incl)
     const bool owns = lane < np && len > 0;
@@ -1101,7 +1097,8 @@ __device__ __forceinline__ void flush(Ctx& C) {
     }
     const bool any_ovf = __ballot(ovf) != 0;
     if (C.lane == 0 && (lo | hi))
-        add_u128(C.a->counts + 2 * C.pi, lo, hi, C.a->plan_flags + C.pi);
+        add_u128(C.a->partial + (blockIdx.x % C.a->copies) * C.a->copy_words + 2 * C.pi, lo, hi,
+                 C.a->plan_flags + C.pi);
     if (C.lane == 0 && any_ovf) atomicOr(C.a->plan_flags + C.pi, 1u);
     C.acc_lo = C.acc_hi = 0;
     C.ovf = false;
@@ -1249,68 +1246,101 @@ __global__ void __launch_bounds__(kBlockThreads, MINB) count_kernel(KArgs a) {
     // cursors, so the grabs spread over several words and every cursor still
     // walks its items in order; a wave starts at its home cursor (its XCD's)
     // and moves on once one runs dry
-    uint32_t rq = home, rtried = 0;
-    // a wave counts as active from its first task until the queues run dry
-    // (and again while it runs a donated task), not per task
+    uint32_t rq = home, sq = home;
+    bool roots_left = true;
+    auto item_at = [&](uint32_t q, uint32_t c) -> uint64_t {
+        if (a.n_plans > kQueues) {
+            // chunk-major: cursor q walks the chunk indices q, q + kQueues, ...
+            // with all plans of one index in a row, so the plans whose
+            // chunks hold the same roots run on one XCD and share its L2
+            const uint64_t ci = (uint64_t)q + (uint64_t)kQueues * (c / a.n_plans);
+            return ci * a.n_plans + c % a.n_plans;
+        }
+        // plan-major: with few plans, cursor q keeps to the plans q mod
+        // n_plans, so a wave's counts stay in its lanes between tasks
+        return (uint64_t)q + (uint64_t)kQueues * c;
+    };
+    // A wave counts as active from its first task until the queues run dry
+    // (and again while it runs a donated task), not per task.  The count is
+    // spread over kActiveLines cache lines: atomics of all waves on one line
+    // take ~14 ns each, which was most of a small launch (8,192 waves, four
+    // updates each: 4 patterns on 2,000 nodes 545 us a launch).
+    uint32_t* const active_line = a.ctl + kCtlActive0 + 32 * (blockIdx.x % kActiveLines);
     bool active = true;
-    if (C.lane == 0) atomicAdd(&a.ctl[kCtlActive], 1u);
+    if (C.lane == 0) atomicAdd(active_line, 1u);
     for (;;) {
         // ---- take a task
+        // (the lane number is made opaque: otherwise the per-lane addresses
+        // below are computed ahead of the loop and kept, spilled, through explore)
+        uint32_t ln = C.lane;
+        asm volatile("" : "+v"(ln));
         uint32_t kind = 2, item = 0;
         bool stop = false;
-        if (C.lane == 0) {
-            // the flag may sit in host memory: poll it on every 32nd task only
-            if (a.cancel && (taken++ & 31u) == 0 && __atomic_load_n(a.cancel, __ATOMIC_RELAXED) != 0) {
-                atomicOr(&a.ctl[kCtlCancelled], 1u);
-                stop = true;
-            }
-            // split queues: the home queue first, then the others (stealing);
-            // the split kernel has finished, so an empty queue stays empty
-            if (!stop && split_left) {
-                split_left = false;
-                for (uint32_t t = 0; t < kQueues; t++) {
-                    const uint32_t q = (home + t) % kQueues;
-                    const uint32_t qcap = a.qbase[q + 1] - a.qbase[q];
-                    uint32_t cnt = __atomic_load_n(&a.ctl[kCtlSplitCount0 + q], __ATOMIC_RELAXED);
-                    cnt = cnt < qcap ? cnt : qcap;
-                    if (__atomic_load_n(&a.ctl[kCtlSplitHead0 + q], __ATOMIC_RELAXED) >= cnt) continue;
-                    const uint32_t it = atomicAdd(&a.ctl[kCtlSplitHead0 + q], 1u);
-                    if (it < cnt) {
-                        kind = 0;
-                        item = a.qbase[q] + it;
-                        split_left = true;
-                        break;
-                    }
-                }
-            }
-            while (!stop && kind == 2 && rtried < kQueues) {
-                const uint32_t c = atomicAdd(&a.ctl[kCtlRootCursor0 + 32 * rq], 1u);
-                uint64_t it;
-                if (a.n_plans > kQueues) {
-                    // chunk-major: cursor q walks the chunk indices q, q + kQueues, ...
-                    // with all plans of one index in a row, so the plans whose
-                    // chunks hold the same roots run on one XCD and share its L2
-                    const uint64_t ci = (uint64_t)rq + (uint64_t)kQueues * (c / a.n_plans);
-                    it = ci * a.n_plans + c % a.n_plans;
-                } else {
-                    // plan-major: with few plans, cursor q keeps to the plans q mod
-                    // n_plans, so a wave's counts stay in its lanes between tasks
-                    it = (uint64_t)rq + (uint64_t)kQueues * c;
-                }
-                if (it < total_chunks) {
-                    kind = 1;
-                    item = (uint32_t)it;
-                } else {
-                    rq = (rq + 1) % kQueues;
-                    rtried++;
-                }
-            }
+        // the flag may sit in host memory: poll it on every 32nd task only
+        if (a.cancel && (taken++ & 31u) == 0) {
+            uint32_t c = 0;
+            if (ln == 0) c = __atomic_load_n(a.cancel, __ATOMIC_RELAXED) != 0;
+            stop = uni(__shfl(c, 0, 64)) != 0;
+            if (stop && ln == 0) atomicOr(&a.ctl[kCtlCancelled], 1u);
         }
-        if (C.lane == 0 && kind == 2 && active) {
-            atomicSub(&a.ctl[kCtlActive], 1u);
+        // split queues: the home queue first, then the others (stealing); the
+        // split kernel has finished, so an empty queue stays empty.  Each head
+        // has a cache line of its own: with all heads on one line the atomics of
+        // 230,000 tasks (four motifs, R-MAT 16) took 10 of a launch's 33 ms.
+        while (!stop && split_left && kind == 2) {
+            const uint32_t qcap = a.qbase[sq + 1] - a.qbase[sq];
+            if (qcap) {
+                uint32_t it = 0, cnt = 0;
+                if (ln == 0) {
+                    it = atomicAdd(&a.ctl[kCtlSplitHead0 + 32 * sq], 1u);
+                    cnt = __atomic_load_n(&a.ctl[kCtlSplitCount0 + sq], __ATOMIC_RELAXED);
+                }
+                it = uni(__shfl(it, 0, 64));
+                cnt = uni(__shfl(cnt, 0, 64));
+                if (it < (cnt < qcap ? cnt : qcap)) {
+                    kind = 0;
+                    item = a.qbase[sq] + it;
+                    break;
+                }
+            }
+            // lane t reads the state of queue sq + 1 + t: one round trip shows
+            // every queue, and a read does not serialise like a failing atomic
+            bool left = false;
+            if (ln < kQueues - 1) {
+                const uint32_t q = (sq + 1 + ln) % kQueues;
+                const uint32_t cap = a.qbase[q + 1] - a.qbase[q];
+                if (cap) {
+                    const uint32_t cnt = __atomic_load_n(&a.ctl[kCtlSplitCount0 + q], __ATOMIC_RELAXED);
+                    left = __atomic_load_n(&a.ctl[kCtlSplitHead0 + 32 * q], __ATOMIC_RELAXED) < (cnt < cap ? cnt : cap);
+                }
+            }
+            const uint64_t m = __ballot(left);
+            if (m) sq = (sq + 1 + (uint32_t)__builtin_ctzll(m)) % kQueues;
+            else split_left = false;
+        }
+        while (!stop && roots_left && kind == 2) {
+            uint32_t c = 0;
+            if (ln == 0) c = atomicAdd(&a.ctl[kCtlRootCursor0 + 32 * rq], 1u);
+            const uint64_t it = item_at(rq, uni(__shfl(c, 0, 64)));
+            if (it < total_chunks) {
+                kind = 1;
+                item = (uint32_t)it;
+                break;
+            }
+            // as above: lane t reads cursor rq + 1 + t
+            bool left = false;
+            const uint32_t q = (rq + 1 + ln) % kQueues;
+            if (ln < kQueues - 1)
+                left = item_at(q, __atomic_load_n(&a.ctl[kCtlRootCursor0 + 32 * q], __ATOMIC_RELAXED)) < total_chunks;
+            const uint64_t m = __ballot(left);
+            if (m) rq = (rq + 1 + (uint32_t)__builtin_ctzll(m)) % kQueues;
+            else roots_left = false;
+        }
+        if (kind == 2 && active) {
+            if (ln == 0) atomicSub(active_line, 1u);
             active = false;
         }
-        if (C.lane == 0 && kind == 2 && !stop) {
+        if (kind == 2 && !stop) {
             // queues drained: wait for donated work while any wave still holds a
             // task.  At most kMaxWaiters waves wait (the others leave at once),
             // and they poll with growing pauses, so waiting waves do not crowd
@@ -1319,33 +1349,54 @@ __global__ void __launch_bounds__(kBlockThreads, MINB) count_kernel(KArgs a) {
             // just before a donation was published and the active count just
             // after its donor finished would leave without it, and the donor
             // itself then takes its entries (the poll checks the queue first).
-            if (atomicAdd(&a.ctl[kCtlIdle], 1u) < kMaxWaiters || C.donated) {
+            bool wait = C.donated;
+            uint32_t idle = 0;
+            if (ln == 0) idle = __atomic_load_n(&a.ctl[kCtlIdle], __ATOMIC_RELAXED);
+            wait = wait || uni(__shfl(idle, 0, 64)) < kMaxWaiters;
+            if (wait) {
+                // between the read and this add a few more waves than
+                // kMaxWaiters may come in; they may wait as well
+                if (ln == 0) atomicAdd(&a.ctl[kCtlIdle], 1u);
                 uint32_t nap = 1;
                 for (uint32_t polls = 0; polls < kIdlePolls; polls++) {
-                    const uint32_t h = __atomic_load_n(&a.ctl[kCtlDonHead], __ATOMIC_RELAXED);
-                    const uint32_t t = __atomic_load_n(&a.ctl[kCtlDonTail], __ATOMIC_RELAXED);
+                    uint32_t h = 0, t = 0;
+                    if (ln == 0) {
+                        h = __atomic_load_n(&a.ctl[kCtlDonHead], __ATOMIC_RELAXED);
+                        t = __atomic_load_n(&a.ctl[kCtlDonTail], __ATOMIC_RELAXED);
+                    }
+                    h = uni(__shfl(h, 0, 64));
+                    t = uni(__shfl(t, 0, 64));
                     if (h < t) {
-                        if (atomicCAS(&a.ctl[kCtlDonHead], h, h + 1) == h) {
+                        uint32_t got = 0;
+                        if (ln == 0) got = atomicCAS(&a.ctl[kCtlDonHead], h, h + 1) == h;
+                        if (uni(__shfl(got, 0, 64))) {
                             kind = 3;
                             item = h;
                             break;
                         }
                         continue;
                     }
-                    if ((polls & 7u) == 7u && __atomic_load_n(&a.ctl[kCtlActive], __ATOMIC_RELAXED) == 0) break;
-                    if (a.cancel && (polls & 63u) == 0 && __atomic_load_n(a.cancel, __ATOMIC_RELAXED) != 0) break;
-                    for (uint32_t z = 0; z < nap; z++) __builtin_amdgcn_s_sleep(64);  // ~4K cycles each
-                    nap = nap < 16 ? nap * 2 : 16;
+                    uint32_t act = 0;
+                    if (ln < kActiveLines)
+                        act = __atomic_load_n(&a.ctl[kCtlActive0 + 32 * ln], __ATOMIC_RELAXED);
+                    if (!__ballot(act != 0)) break;
+                    if (a.cancel && (polls & 63u) == 0) {
+                        uint32_t c = 0;
+                        if (ln == 0) c = __atomic_load_n(a.cancel, __ATOMIC_RELAXED) != 0;
+                        if (uni(__shfl(c, 0, 64))) break;
+                    }
+                    // pauses double from ~0.2 us, so a launch ends within about
+                    // twice its last task's remaining time or the longest pause
+                    for (uint32_t z = 0; z < nap; z++) __builtin_amdgcn_s_sleep(8);
+                    nap = nap < kNapMax ? nap * 2 : kNapMax;
                 }
+                if (ln == 0) atomicSub(&a.ctl[kCtlIdle], 1u);
             }
-            atomicSub(&a.ctl[kCtlIdle], 1u);
         }
-        if (C.lane == 0 && kind == 3) {
-            atomicAdd(&a.ctl[kCtlActive], 1u);
+        if (kind == 3) {
+            if (ln == 0) atomicAdd(active_line, 1u);
             active = true;
         }
-        kind = uni(__shfl(kind, 0, 64));
-        item = uni(__shfl(item, 0, 64));
         if (kind == 2) break;
         uint32_t n0 = 0, start = 1;
         // counts of consecutive tasks of one plan stay in the lanes'
@@ -1436,7 +1487,7 @@ __global__ void __launch_bounds__(kBlockThreads, MINB) count_kernel(KArgs a) {
         if (C.stop) break;
     }
     // a wave that was counted as active must not stay so after a cancel
-    if (C.lane == 0 && C.stop && active) atomicSub(&a.ctl[kCtlActive], 1u);
+    if (C.lane == 0 && C.stop && active) atomicSub(active_line, 1u);
     flush(C);
 }
 
@@ -1490,7 +1541,7 @@ __global__ void init_kernel(InitArgs a) {
     if (a.zero_ctl) {
         for (uint32_t i = tid; i < kCtlWords; i += nthr) a.ctl[i] = 0;
         for (uint32_t i = tid; i < a.n_plans; i += nthr) a.plan_flags[i] = 0;
-        for (uint32_t i = tid; i < 2 * a.n_plans; i += nthr) a.counts[i] = 0;
+        for (uint32_t i = tid; i < a.partial_words; i += nthr) a.partial[i] = 0;
         // the workspace is reused across launches (and by the caller's
         // allocator): a slot is ready only once this launch publishes it
         for (uint32_t i = tid; i < a.don_cap; i += nthr) a.don[(uint64_t)i * kDonWords + 1] = 0;
@@ -1498,7 +1549,7 @@ __global__ void init_kernel(InitArgs a) {
     }
 }
 
-// Per-plan status from the flags the count kernel raised.
+// Per-plan totals, and status from the flags the count kernel raised.
 __global__ void finalize_kernel(KArgs a) {
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < a.n_plans; i += gridDim.x * blockDim.x) {
         int32_t st = 0;
@@ -1506,15 +1557,19 @@ __global__ void finalize_kernel(KArgs a) {
         else if (a.ctl[kCtlQueueFull]) st = -6;
         else if (a.ctl[kCtlCancelled]) st = -7;
         else if (a.plan_flags[i] & 1u) st = -5;
-        const uint32_t m = a.plans[i].sym_mult;
-        if (m > 1 && st == 0) {
-            // one embedding per orbit was counted: scale the 128-bit total
-            unsigned long long* c = a.counts + 2 * i;
-            unsigned long long lo = c[0], hi = c[1];
-            if (u128_scale(lo, hi, m)) st = -5;
-            c[0] = lo;
-            c[1] = hi;
+        // the copies' totals, added up
+        unsigned long long lo = 0, hi = 0;
+        bool big = false;
+        for (uint32_t c = 0; c < a.copies; c++) {
+            const unsigned long long* p = a.partial + (uint64_t)c * a.copy_words + 2 * i;
+            if (u128_add(lo, hi, p[0], p[1])) big = true;
         }
+        if (big && st == 0) st = -5;
+        const uint32_t m = a.plans[i].sym_mult;
+        // one embedding per orbit was counted: scale the 128-bit total
+        if (m > 1 && st == 0 && u128_scale(lo, hi, m)) st = -5;
+        a.counts[2 * i] = lo;
+        a.counts[2 * i + 1] = hi;
         a.status[i] = st;
     }
 }

@@ -18,9 +18,18 @@ constexpr uint32_t kMergeRatio = 16;  // ... and within this length ratio -> mer
 
 // Control words at the start of the workspace.
 constexpr uint32_t kQueues = 8;  // split-task queues, one per XCD (8 XCDs on MI355X)
+constexpr uint32_t kActiveLines = 64;  // one per lane of a waiting wave
+constexpr uint32_t kMaxWaiters = 512;  // waves that wait for donated work; the others leave
 constexpr uint32_t kDonWords = 8;  // donated task: plan | depth << 16, ready flag, prefix nodes [6]
 constexpr uint32_t kDonCap = 1u << 18;  // donated-task slots per launch
-constexpr uint32_t kDonCapStatic = 1u << 14;  // ... in launches on the static scratch array
+constexpr uint32_t kDonCapStatic = (1u << 14) - (1u << 11);  // ... in launches on the static scratch array
+// Copies of the count totals: 32 for up to 64 plans, then fewer (plans spread
+// the updates by themselves); a copy starts on a cache line of its own.
+inline uint32_t count_copies(uint32_t n_plans) {
+    const uint32_t c = 2048u / n_plans;
+    return c < 1 ? 1 : (c > 32 ? 32 : c);
+}
+inline uint32_t count_copy_words(uint32_t n_plans) { return (2 * n_plans + 15u) / 16u * 16u; }
 
 // The static scratch array of xm_count_static (file scope in count.hip): one
 // copy per device, held until the process ends.
@@ -43,15 +52,18 @@ enum Ctl : uint32_t {
     kCtlCancelled = 3,    // a wave saw the cancel flag
     kCtlQueueFull = 4,    // split queue overflow (cannot happen with a sized workspace)
     kCtlBadPlan = 5,      // a level had more constraints than the layout holds (cannot happen)
-    kCtlSplitHead0 = 8,   // [kQueues]: next item of split queue q
     kCtlSplitCount0 = 16, // [kQueues]: items the split kernel wrote to queue q
     // the words idle waves poll sit on cache lines of their own
-    kCtlActive = 64,      // waves in a work phase (from their first task until the queues ran dry)
     kCtlIdle = 96,        // waves waiting for donated tasks
     kCtlDonHead = 128,    // next donated task to take
     kCtlDonTail = 160,    // donated-task slots reserved
     kCtlRootCursor0 = 192,  // [kQueues], 32 words apart: cursor q hands out root items q, q + 8, ...
-    kCtlWords = 192 + 32 * kQueues
+    // [kActiveLines], 32 words apart: waves in a work phase (from their first
+    // task until the queues ran dry); a block counts in line block mod kActiveLines
+    kCtlActive0 = 192 + 32 * kQueues,
+    // [kQueues], 32 words apart: next item of split queue q
+    kCtlSplitHead0 = kCtlActive0 + 32 * kActiveLines,
+    kCtlWords = kCtlSplitHead0 + 32 * kQueues
 };
 
 struct DevGraph {
@@ -113,6 +125,11 @@ struct KArgs {
     uint32_t merge_ratio;
     uint32_t wave_words;        // scratch words per wave
     uint32_t* scratch;          // n_waves * wave_words
+    // Waves add their totals to copy (block mod copies) of the counts, copy c
+    // at word c * copy_words of partial; the finalize kernel adds the copies up.
+    // On one copy the atomics of 8,192 waves on a line took ~0.1 ms a launch.
+    unsigned long long* partial;
+    uint32_t copies, copy_words;
     unsigned long long* counts; // 2 per plan
     int32_t* status;            // 1 per plan
     const int32_t* cancel;      // nullable
@@ -126,7 +143,8 @@ struct InitArgs {
     uint32_t zero_ctl;          // 1: also clear control words, flags and counts
     uint32_t* ctl;
     uint32_t* plan_flags;
-    unsigned long long* counts;
+    unsigned long long* partial;  // count copies
+    uint32_t partial_words;
     uint32_t* don;              // donated-task slots: their ready words are cleared
     uint32_t don_cap;
     unsigned long long* list_count;  // listing counter (NULL: none)

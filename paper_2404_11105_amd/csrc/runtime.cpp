@@ -99,9 +99,9 @@ int plan_device_desc(xm_plan_t* p, int dev, const PlanDesc** out) {
 }
 
 struct Layout {
-    uint32_t chunk, split, split_work, cap, waves_per_cu, n_waves, n_blocks, e_max, maxc, merge_min, don_cap;
+    uint32_t chunk, split, split_work, cap, waves_per_cu, n_waves, n_blocks, launch_blocks, e_max, maxc, merge_min, don_cap;
     bool nonlinear;
-    size_t off_ctl, off_flags, off_table, off_split, off_don, off_scratch, total;
+    size_t off_ctl, off_flags, off_partial, off_table, off_split, off_don, off_scratch, total;
     uint32_t split_cap, wave_words, lds_words;
     uint32_t qbase[xm::kQueues + 1];
 };
@@ -279,6 +279,15 @@ int make_layout(const xm_graph_t* g, uint32_t n_plans, const xm_plan_t* const* p
     }
     if (items > 0xFFFFFFF0ull) return fail(XM_ERR_INVALID, "split queue too large; raise split_work");
     L.split_cap = (uint32_t)std::max<uint64_t>(items, 1);
+    {
+        // a wave without a task of its own only helps as a receiver of donated
+        // work, and at most kMaxWaiters waves wait for that: a small launch
+        // starts no more blocks than its items and those waiters need
+        const uint64_t n_src = (o && o->roots_dev) ? o->n_roots : g->n;
+        const uint64_t tasks = (n_src + L.chunk - 1) / L.chunk * n_plans + items + xm::kMaxWaiters;
+        L.launch_blocks =
+            (uint32_t)std::min<uint64_t>(L.n_blocks, (tasks + xm::kWavesPerBlock - 1) / xm::kWavesPerBlock);
+    }
     L.qbase[0] = 0;
     for (uint32_t q = 0; q < xm::kQueues; q++) L.qbase[q + 1] = L.qbase[q] + (uint32_t)qc[q];
     L.wave_words = L.e_max * xm::kLvlArrays * L.cap;
@@ -287,6 +296,8 @@ int make_layout(const xm_graph_t* g, uint32_t n_plans, const xm_plan_t* const* p
     off = align256(off + xm::kCtlWords * 4);
     L.off_flags = off;
     off = align256(off + (size_t)n_plans * 4);
+    L.off_partial = off;
+    off = align256(off + (size_t)xm::count_copies(n_plans) * xm::count_copy_words(n_plans) * 8);
     L.off_table = off;
     off = align256(off + (size_t)n_plans * sizeof(PlanDesc));
     L.off_split = off;
@@ -382,6 +393,9 @@ int enqueue_count(const xm_graph_t* g, uint32_t n_plans, const xm_plan_t* const*
     a.wave_words = L.wave_words;
     a.scratch = reinterpret_cast<uint32_t*>(base + L.off_scratch);
     a.counts = reinterpret_cast<unsigned long long*>(counts);
+    a.partial = reinterpret_cast<unsigned long long*>(base + L.off_partial);
+    a.copies = xm::count_copies(n_plans);
+    a.copy_words = xm::count_copy_words(n_plans);
     a.status = status;
     a.cancel = o ? o->cancel_dev : nullptr;
     const bool listing = o && (o->struct_size == 0 || o->struct_size >= sizeof(xm_count_opts)) && o->list_dev;
@@ -406,7 +420,8 @@ int enqueue_count(const xm_graph_t* g, uint32_t n_plans, const xm_plan_t* const*
         ia.zero_ctl = 1;
         ia.ctl = a.ctl;
         ia.plan_flags = a.plan_flags;
-        ia.counts = a.counts;
+        ia.partial = a.partial;
+        ia.partial_words = a.copies * a.copy_words;
         ia.don = a.don;
         ia.don_cap = a.don_cap;
         ia.list_count = a.list_count;
@@ -428,7 +443,8 @@ int enqueue_count(const xm_graph_t* g, uint32_t n_plans, const xm_plan_t* const*
         ia.zero_ctl = (first == 0) ? 1 : 0;
         ia.ctl = a.ctl;
         ia.plan_flags = a.plan_flags;
-        ia.counts = a.counts;
+        ia.partial = a.partial;
+        ia.partial_words = a.copies * a.copy_words;
         ia.don = a.don;
         ia.don_cap = a.don_cap;
         ia.list_count = a.list_count;
@@ -436,7 +452,7 @@ int enqueue_count(const xm_graph_t* g, uint32_t n_plans, const xm_plan_t* const*
     }
     hipEvent_t ev0 = o ? static_cast<hipEvent_t>(o->ev_kernel_start) : nullptr;
     hipEvent_t ev1 = o ? static_cast<hipEvent_t>(o->ev_kernel_stop) : nullptr;
-    hipError_t e = xm::launch_count(inits.data(), (int)inits.size(), a, L.n_blocks, stream, ev0, ev1);
+    hipError_t e = xm::launch_count(inits.data(), (int)inits.size(), a, L.launch_blocks, stream, ev0, ev1);
     if (e != hipSuccess) return hip_fail(e, "kernel launch");
     return XM_OK;
 }
