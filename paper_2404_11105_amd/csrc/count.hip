@@ -589,7 +589,7 @@ __device__ __forceinline__ void wide_step(const Ctx& C, const LK& D, uint32_t in
 // 134 ms, C5 + chord on R-MAT 20 (1/256 of the roots) 229 and 97 ms, 96 plans on
 // R-MAT 22 614 and 385 ms, four unreduced motifs on R-MAT 16 162 and 157 ms (bound
 // by the row gathers either way: one TD clock per 32-byte sector a load touches).
-template <class F>
+template <bool FOUR, class F>
 __device__ __forceinline__ void wide_scan(const Ctx& C, const LK& D, uint32_t inj, uint32_t lv, uint32_t ns,
                                           uint32_t j, gptr base, uint32_t len, F&& emit) {
     gptr r0 = base, r1 = base;
@@ -608,11 +608,9 @@ __device__ __forceinline__ void wide_scan(const Ctx& C, const LK& D, uint32_t in
         }
     }
     uint32_t i0 = 0;
-    for (; i0 + 128 < len; i0 += 256) wide_step<4>(C, D, inj, lv, j, base, len, i0, nrow, r0, r1, rest, emit);
-    for (; i0 < len; i0 += 128) {
-        if (i0 + 64 < len) wide_step<2>(C, D, inj, lv, j, base, len, i0, nrow, r0, r1, rest, emit);
-        else wide_step<1>(C, D, inj, lv, j, base, len, i0, nrow, r0, r1, rest, emit);
-    }
+    if (FOUR)
+        for (; i0 + 128 < len; i0 += 256) wide_step<4>(C, D, inj, lv, j, base, len, i0, nrow, r0, r1, rest, emit);
+    for (; i0 < len; i0 += 128) wide_step<2>(C, D, inj, lv, j, base, len, i0, nrow, r0, r1, rest, emit);
 }
 
 // Whether bound node y of this lane's partial match lies in the lane's base
@@ -633,9 +631,120 @@ __device__ __forceinline__ bool bound_in_set(const Ctx& C, uint32_t ns, uint32_t
 // injectivity: leaf passes settle that per partial match).
 __device__ __forceinline__ uint32_t wide_count(const Ctx& C, const LK& D, uint32_t lv, uint32_t ns, uint32_t j) {
     uint32_t cnt = 0;
-    wide_scan(C, D, 0u, lv, ns, j, join_ptr(uni(C.s.base_lo[j]), uni(C.s.base_hi[j])), uni(C.s.base_len[j]),
+    wide_scan<true>(C, D, 0u, lv, ns, j, join_ptr(uni(C.s.base_lo[j]), uni(C.s.base_hi[j])), uni(C.s.base_len[j]),
               [&](uint32_t, bool ok) { cnt += (uint32_t)__popcll(__ballot(ok)); });
     return cnt;
+}
+
+// A window parent of a leaf pass as its lane sees it: base list, and up to two
+// dense rows to test (when its probes are nothing else).
+struct Par {
+    uint32_t lo, hi, len;        // base list
+    uint32_t n_rows;             // rows to test
+    uint32_t r0lo, r0hi, r1lo, r1hi;
+    bool rows_only;              // no sorted-list probe, at most two rows
+};
+__device__ __forceinline__ Par parent_view(const Ctx& C, uint32_t ns, uint32_t len) {
+    const uint32_t lane = C.lane;
+    Par p;
+    p.lo = C.s.base_lo[lane];
+    p.hi = C.s.base_hi[lane];
+    p.len = len;
+    p.n_rows = 0;
+    p.r0lo = p.r0hi = p.r1lo = p.r1hi = 0;
+    p.rows_only = true;
+    for (uint32_t k = 0; k < ns; k++) {
+        const uint32_t l = C.s.slot_len[k * 64 + lane];
+        if (l == kSkip) continue;
+        if (l == 0) p.len = 0;  // an empty list holds nothing
+        if (l != kRowLen || p.n_rows == 2) {
+            p.rows_only = false;
+            continue;
+        }
+        const uint32_t lo = C.s.slot_lo[k * 64 + lane], hi = C.s.slot_hi[k * 64 + lane];
+        if (p.n_rows == 0) {
+            p.r0lo = p.r1lo = lo;
+            p.r0hi = p.r1hi = hi;
+        } else {
+            p.r1lo = lo;
+            p.r1hi = hi;
+        }
+        p.n_rows++;
+    }
+    return p;
+}
+
+__device__ __forceinline__ uint32_t from_lane(uint32_t v, uint32_t j) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)j);
+}
+
+// Count, for every lane (window parent) in `todo`, the base elements that are
+// in its one or two rows; add(j, n) is called with the counts.  The parents'
+// lists are cut into chunks of two tiles, and two chunks are in flight at a
+// time, of one parent or of two, so short lists too keep four base loads and
+// four row loads outstanding.  Everything about a chunk is scalar, read from
+// its lane's registers: ~6 vector instructions a tile.  Measured against one
+// parent at a time (wide_scan): TT4 + pendant on R-MAT 18 134 and 127 ms (best
+// runs 129 and 103), four motifs on R-MAT 16 21.5 and 20.1, unreduced 158 and 154.
+template <class F>
+__device__ __forceinline__ void chunk_scan(const Ctx& C, const Par& P, uint64_t todo, F&& add) {
+    struct Chunk {
+        gptr base, r0, r1;
+        uint32_t j, n, rows;
+    };
+    const uint32_t lane = C.lane;
+    uint32_t i0 = 0, left = 0;
+    Chunk cur{};
+    auto next = [&](Chunk& c) {
+        if (i0 >= left) {
+            if (!todo) {
+                c = cur;
+                c.n = 0;
+                return;
+            }
+            cur.j = (uint32_t)__builtin_ctzll(todo);
+            todo &= todo - 1;
+            left = from_lane(P.len, cur.j);
+            cur.base = join_ptr(from_lane(P.lo, cur.j), from_lane(P.hi, cur.j));
+            cur.r0 = join_ptr(from_lane(P.r0lo, cur.j), from_lane(P.r0hi, cur.j));
+            cur.rows = from_lane(P.n_rows, cur.j);
+            cur.r1 = cur.r0;
+            if (cur.rows > 1) cur.r1 = join_ptr(from_lane(P.r1lo, cur.j), from_lane(P.r1hi, cur.j));
+            i0 = 0;
+        }
+        c = cur;
+        c.base = cur.base + i0;
+        c.n = left - i0 < 128u ? left - i0 : 128u;
+        i0 += 128;
+    };
+    while (todo || i0 < left) {
+        Chunk c[2];
+        next(c[0]);
+        next(c[1]);
+        uint32_t x[4], w[4];
+        uint64_t in[4];
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            // lanes past the end read the last element again
+            const uint32_t n = c[u >> 1].n, off = (u & 1) * 64u;
+            const uint32_t i = off + lane, last = n ? n - 1 : 0u;
+            x[u] = c[u >> 1].base[i < last ? i : last];
+            in[u] = n >= off + 64u ? ~0ull : (n > off ? (1ull << (n - off)) - 1ull : 0ull);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; u++) w[u] = c[u >> 1].r0[x[u] >> 5];
+#pragma unroll
+        for (int u = 0; u < 4; u++) in[u] &= __ballot(__builtin_amdgcn_ubfe(w[u], x[u], 1u) != 0);
+        if (c[0].rows > 1 || c[1].rows > 1) {
+            // (a chunk with one row tests it again)
+#pragma unroll
+            for (int u = 0; u < 4; u++) w[u] = c[u >> 1].r1[(in[u] >> lane) & 1u ? x[u] >> 5 : 0u];
+#pragma unroll
+            for (int u = 0; u < 4; u++) in[u] &= __ballot(__builtin_amdgcn_ubfe(w[u], x[u], 1u) != 0);
+        }
+        add(c[0].j, (uint32_t)(__popcll(in[0]) + __popcll(in[1])));
+        add(c[1].j, (uint32_t)(__popcll(in[2]) + __popcll(in[3])));
+    }
 }
 
 // Expand one window of level lv from the parents in level lv-1.  Returns the
@@ -683,7 +792,7 @@ __device__ __forceinline__ uint32_t expand(Ctx& C, uint32_t lv) {
             const uint32_t off = j0 == 0 ? pofs : 0u;
             const gptr base = join_ptr(uni(C.s.base_lo[j0]), uni(C.s.base_hi[j0])) + off;
             const uint32_t n = uni(__shfl(len, (int)j0, 64));
-            wide_scan(C, D, D.inj, lv, ns, j0, base, n, [&](uint32_t x, bool ok) {
+            wide_scan<false>(C, D, D.inj, lv, ns, j0, base, n, [&](uint32_t x, bool ok) {
                 const uint64_t m = __ballot(ok);
                 if (ok) {
                     const uint32_t pos = nout + rank_below(m);
@@ -857,8 +966,11 @@ __device__ __forceinline__ void leaf_masks(Ctx& C, uint32_t nb, uint32_t p, bool
             uint32_t len = phase_a<true>(C, K, nb, p, pv, false);
             const uint32_t ns = n_slots(K);
             // long base lists are scanned one by one after the flattened pass
-            uint64_t wide = __ballot(len >= kWideMin);
-            if (len >= kWideMin) len = 0;
+            const Par P1 = parent_view(C, ns, len);
+            const bool wd = len >= kWideMin && !K.deg_check;
+            const uint64_t chunks = __ballot(wd && P1.rows_only && P1.n_rows > 0 && P1.len > 0);
+            uint64_t wide = __ballot(wd && P1.len > 0) & ~chunks;
+            if (wd) len = 0;
             const uint32_t incl = scan_incl(len, lane);
             C.s.incl[lane] = incl;
             const uint32_t T = uni(__shfl(incl, 63, 64));
@@ -882,6 +994,7 @@ __device__ __forceinline__ void leaf_masks(Ctx& C, uint32_t nb, uint32_t p, bool
                 const uint64_t ba = __ballot(oka), bb = __ballot(okb);
                 if (owns) h += own_count(ba, start, len, t0) + own_count(bb, start, len, t0 + 64);
             }
+            if (chunks) chunk_scan(C, P1, chunks, [&](uint32_t j, uint32_t n) { h += lane == j ? n : 0u; });
             for (; wide; wide &= wide - 1) {
                 const uint32_t j = (uint32_t)__builtin_ctzll(wide);
                 const uint32_t cnt = wide_count(C, K, nb, ns, j);
@@ -1026,8 +1139,11 @@ __device__ __forceinline__ void count_leaves(Ctx& C, uint32_t lv, uint32_t npref
             }
             uint64_t bigmask = __ballot(big);
             // other long base lists are scanned one by one (listing stays flattened)
-            uint64_t wide = __ballot(len >= kWideMin && !big && !listing);
-            if (big || (len >= kWideMin && !listing)) len = 0;
+            const Par P1 = parent_view(C, ns, len);
+            const bool wd = len >= kWideMin && !big && !listing && !S.deg_check;
+            const uint64_t chunks = __ballot(wd && P1.rows_only && P1.n_rows > 0 && P1.len > 0);
+            uint64_t wide = __ballot(wd && P1.len > 0) & ~chunks;
+            if (big || wd) len = 0;
             (void)nsig;
             const uint32_t incl = scan_incl(len, lane);
             C.s.incl[lane] = incl;
@@ -1056,6 +1172,7 @@ __device__ __forceinline__ void count_leaves(Ctx& C, uint32_t lv, uint32_t npref
                 lin += (unsigned long long)(__popcll(ma) + __popcll(mb));
                 if (listing) write_rows(C, nb, ma, mb, ja, xa, oka, jb, xb, okb);
             }
+            if (chunks) chunk_scan(C, P1, chunks, [&](uint32_t, uint32_t n) { lin += n; });
             for (; wide; wide &= wide - 1)
                 lin += wide_count(C, S, nb, ns, (uint32_t)__builtin_ctzll(wide));
             // bound nodes the leaf may not take were counted if they are in the set
