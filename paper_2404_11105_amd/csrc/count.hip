@@ -43,10 +43,14 @@ constexpr uint32_t kComplete = 0x80000000u;
 // (wide_scan).  Measured at 32 / 64 / 128: unreduced motifs on R-MAT 16 192 /
 // 174 / 181 ms, 96 plans on R-MAT 22 414 / 393 / 392 ms: one tile per scan is
 // the shortest list that pays for reading the parent's probes.
-#ifndef XM_WIDE_MIN
-#define XM_WIDE_MIN 64
-#endif
-constexpr uint32_t kWideMin = XM_WIDE_MIN;
+constexpr uint32_t kWideMin = 64;
+// Words a base element is worth in the dense head of a row.  A 16-byte row load
+// takes 17 TD clocks for 256 words, a row test of an element up to one clock
+// and, when it misses L2, a whole line.  Measured at 2 / 3 / 4 / 8 (none): 96
+// plans on R-MAT 22 347 / 348 / 351 / 373 (382) ms, C5 + chord on R-MAT 20 72 /
+// - / 72 / 75 (88), motifs on R-MAT 16 19.7 / 20.4 / 21.2 / 22.3 (21.3),
+// unreduced 154 / 156 / 160 / 182 (155).
+constexpr uint32_t kDenseWords = 2;
 
 __device__ __forceinline__ uint32_t uni(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
 __device__ __forceinline__ uint32_t lane_id() {
@@ -298,13 +302,18 @@ __device__ __forceinline__ void sym_trim(const Lds& s, uint32_t gt, uint32_t lt,
 // Phase A of a level: lane = one partial match (parent) of the window.  Walks
 // the parent chain into LDS (bound nodes, ancestor indices), picks the base
 // list and writes the probes (the other constraint lists, long ones as their
-// dense rows) into the parent's probe slots.  Returns the base length.
+// dense rows) into the parent's probe slots.  Returns the base length; for a
+// leaf pass brow becomes the dense row of the base list (kSkip: none) and bskip
+// the elements cut off its front.
 template <bool IS_SIG>
-__device__ __forceinline__ uint32_t phase_a(Ctx& C, const LK& D, uint32_t lv, uint32_t p, bool pv, bool walk) {
+__device__ __forceinline__ uint32_t phase_a(Ctx& C, const LK& D, uint32_t lv, uint32_t p, bool pv, bool walk, uint32_t& brow,
+                                            uint32_t& bskip) {
     const KArgs& a = *C.a;
     const DevGraph& g = a.g;
     const uint32_t lane = C.lane;
     uint32_t len = 0;
+    brow = kSkip;
+    bskip = 0;
     if (!pv) {
         C.s.base_len[lane] = 0;
         return 0;
@@ -385,6 +394,10 @@ __device__ __forceinline__ uint32_t phase_a(Ctx& C, const LK& D, uint32_t lv, ui
         }
         base = adj_of(g, D.dir(bc)) + bo;
         len = best;
+        if (IS_SIG && len >= g.row_min) {
+            const uint2 r = g.row_of[C.s.bound[D.lvl(bc) * 64 + lane]];
+            brow = D.dir(bc) ? r.y : r.x;
+        }
         if (!IS_SIG && lv == 1) {
             // a root carries its first-level range [lo, hi)
             Lvl F0 = lvl_arrays(C.scr, a.cap, 0);
@@ -397,7 +410,11 @@ __device__ __forceinline__ uint32_t phase_a(Ctx& C, const LK& D, uint32_t lv, ui
     }
     for (; k < D.n_cons; k++) put(k, safe_ptr(g), kSkip);
     // symmetry breaking: the base is sorted, so its candidates are a range
-    if (D.gt) sym_trim(C.s, D.gt, D.lt, lv, lane, base, len);
+    if (D.gt) {
+        const uint32_t* whole = base;
+        sym_trim(C.s, D.gt, D.lt, lv, lane, base, len);
+        bskip = (uint32_t)(base - whole);
+    }
     const uint64_t bv = reinterpret_cast<uint64_t>(base);
     C.s.base_lo[lane] = (uint32_t)bv;
     C.s.base_hi[lane] = (uint32_t)(bv >> 32);
@@ -588,7 +605,7 @@ __device__ __forceinline__ void wide_step(const Ctx& C, const LK& D, uint32_t in
 // Measured, flattened only and with this: TT4 + pendant on R-MAT 18 313 and
 // 134 ms, C5 + chord on R-MAT 20 (1/256 of the roots) 229 and 97 ms, 96 plans on
 // R-MAT 22 614 and 385 ms, four unreduced motifs on R-MAT 16 162 and 157 ms (bound
-// by the row gathers either way: one TD clock per 32-byte sector a load touches).
+// by the row gathers' misses in L2 either way).
 template <bool FOUR, class F>
 __device__ __forceinline__ void wide_scan(const Ctx& C, const LK& D, uint32_t inj, uint32_t lv, uint32_t ns,
                                           uint32_t j, gptr base, uint32_t len, F&& emit) {
@@ -747,6 +764,142 @@ __device__ __forceinline__ void chunk_scan(const Ctx& C, const Par& P, uint64_t 
     }
 }
 
+// The dense part of a parent's base list: the ids [xlo, xhi) in the words
+// [w0, w1) (multiples of 4) of its row.
+struct Dense {
+    uint32_t lo, hi;  // the row
+    uint32_t w0, w1, xlo, xhi;
+};
+
+// Splits parent P's base list (dense row brow, bskip elements cut off its
+// front) into a dense part, taken from P, and the rest, which stays.  A row's
+// head is dense where its list's ids are (row_pre: words and elements of the
+// head); intersecting words there reads both rows in order, 16 bytes a lane,
+// where the elements would each touch a sector of the probed row.
+__device__ __forceinline__ Dense take_dense(const Ctx& C, const LK& D, uint32_t nb, uint32_t brow, uint32_t bskip,
+                                            Par& P) {
+    const DevGraph& g = C.a->g;
+    Dense d{};
+    if (brow == kSkip) return d;
+    const uint2 pre = g.row_pre[brow];  // words, elements
+    const uint64_t row = reinterpret_cast<uint64_t>(g.rows + (uint64_t)brow * g.row_words);
+    d.lo = (uint32_t)row;
+    d.hi = (uint32_t)(row >> 32);
+    d.w1 = pre.x;
+    d.xhi = pre.x * 32u;
+    uint32_t take = pre.y > bskip ? pre.y - bskip : 0u;
+    take = take < P.len ? take : P.len;
+    if (D.gt) {
+        uint32_t lo = 0xFFFFFFFFu, hi = 0;
+        for (uint32_t l = 0; l < nb; l++)
+            if ((D.gt >> l) & 1u) {
+                const uint32_t b = C.s.bound[l * 64 + C.lane];
+                lo = b < lo ? b : lo;
+                hi = b > hi ? b : hi;
+            }
+        if (D.lt) {
+            d.xhi = lo < d.xhi ? lo : d.xhi;
+            d.w1 = (d.xhi + 127u) / 128u * 4u;
+        } else {
+            d.xlo = hi + 1u;
+            d.w0 = d.xlo / 128u * 4u;
+        }
+    }
+    if (d.w0 >= d.w1 || take * kDenseWords < d.w1 - d.w0) {
+        d.w0 = d.w1 = 0;
+        return d;
+    }
+    const uint64_t rest = (((uint64_t)P.hi << 32) | P.lo) + 4ull * take;
+    P.lo = (uint32_t)rest;
+    P.hi = (uint32_t)(rest >> 32);
+    P.len -= take;
+    return d;
+}
+
+// Count, for every lane in `todo`, the bits common to its dense part and its
+// one or two rows.  Chunks of 256 words, two in flight; add(j, v) is called
+// with each lane's share v of a chunk's count.
+template <class F>
+__device__ __forceinline__ void word_scan(const Ctx& C, const Par& P, const Dense& Dn, bool trim, uint64_t todo,
+                                          F&& add) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
+    typedef const __attribute__((address_space(1))) u32x4* gptr4;
+    struct Chunk {
+        gptr base, r0, r1;
+        uint32_t j, w, end, xlo, xhi, rows;
+    };
+    const uint32_t lane = C.lane;
+    Chunk cur{};
+    auto next = [&](Chunk& c) {
+        if (cur.w >= cur.end) {
+            if (!todo) {
+                c = cur;
+                return;
+            }
+            cur.j = (uint32_t)__builtin_ctzll(todo);
+            todo &= todo - 1;
+            cur.base = join_ptr(from_lane(Dn.lo, cur.j), from_lane(Dn.hi, cur.j));
+            cur.w = from_lane(Dn.w0, cur.j);
+            cur.end = from_lane(Dn.w1, cur.j);
+            cur.r0 = join_ptr(from_lane(P.r0lo, cur.j), from_lane(P.r0hi, cur.j));
+            cur.rows = from_lane(P.n_rows, cur.j);
+            cur.r1 = cur.r0;
+            if (cur.rows > 1) cur.r1 = join_ptr(from_lane(P.r1lo, cur.j), from_lane(P.r1hi, cur.j));
+            if (trim) {
+                cur.xlo = from_lane(Dn.xlo, cur.j);
+                cur.xhi = from_lane(Dn.xhi, cur.j);
+            }
+        }
+        c = cur;
+        cur.w += 256;
+    };
+    while (todo || cur.w < cur.end) {
+        Chunk c[2];
+        next(c[0]);
+        next(c[1]);
+        u32x4 b[2], r[2];
+        bool in[2];
+        uint32_t w[2];
+#pragma unroll
+        for (int u = 0; u < 2; u++) {
+            w[u] = c[u].w + 4 * lane;
+            in[u] = w[u] < c[u].end;
+            const uint32_t at = in[u] ? w[u] : 0u;
+            b[u] = *(gptr4)(c[u].base + at);
+            r[u] = *(gptr4)(c[u].r0 + at);
+        }
+        uint32_t n[2];
+#pragma unroll
+        for (int u = 0; u < 2; u++) b[u] &= r[u];
+        if (c[0].rows > 1 || c[1].rows > 1) {
+            // (a chunk with one row takes it again)
+#pragma unroll
+            for (int u = 0; u < 2; u++) b[u] &= *(gptr4)(c[u].r1 + (in[u] ? w[u] : 0u));
+        }
+        if (trim) {
+            // keep the ids in [xlo, xhi)
+#pragma unroll
+            for (int u = 0; u < 2; u++)
+#pragma unroll
+                for (int e = 0; e < 4; e++) {
+                    const uint32_t x0 = (w[u] + (uint32_t)e) * 32u;
+                    const uint32_t below = c[u].xhi > x0 ? c[u].xhi - x0 : 0u;     // ids of the word under xhi
+                    const uint32_t under = c[u].xlo > x0 ? c[u].xlo - x0 : 0u;     // ids of the word under xlo
+                    const uint32_t hm = below >= 32u ? ~0u : (1u << below) - 1u;
+                    const uint32_t lm = under >= 32u ? ~0u : (1u << under) - 1u;
+                    b[u][e] &= hm & ~lm;
+                }
+        }
+#pragma unroll
+        for (int u = 0; u < 2; u++) {
+            n[u] = (uint32_t)(__popc(b[u].x) + __popc(b[u].y) + __popc(b[u].z) + __popc(b[u].w));
+            n[u] = in[u] ? n[u] : 0u;
+        }
+        add(c[0].j, n[0]);
+        add(c[1].j, n[1]);
+    }
+}
+
 // Expand one window of level lv from the parents in level lv-1.  Returns the
 // number of children written to level lv's buffer.
 __device__ __forceinline__ uint32_t expand(Ctx& C, uint32_t lv) {
@@ -759,7 +912,8 @@ __device__ __forceinline__ uint32_t expand(Ctx& C, uint32_t lv) {
     const uint32_t pofs = uni(st[8 + lv]);
     const uint32_t p = cur + lane;
     const bool pv = p < nparents;
-    uint32_t len = phase_a<false>(C, D, lv, p, pv, true);
+    uint32_t brow, bskip;
+    uint32_t len = phase_a<false>(C, D, lv, p, pv, true, brow, bskip);
     if (pv && lane == 0) len -= pofs;
     uint32_t incl = scan_incl(len, lane);
     C.s.incl[lane] = incl;
@@ -963,13 +1117,17 @@ __device__ __forceinline__ void leaf_masks(Ctx& C, uint32_t nb, uint32_t p, bool
                     if (((K.inj >> b) & 1u) && contains(L, l, C.s.bound[b * 64 + lane])) h -= 1;
             }
         } else {
-            uint32_t len = phase_a<true>(C, K, nb, p, pv, false);
+            uint32_t brow, bskip;
+            uint32_t len = phase_a<true>(C, K, nb, p, pv, false, brow, bskip);
             const uint32_t ns = n_slots(K);
             // long base lists are scanned one by one after the flattened pass
-            const Par P1 = parent_view(C, ns, len);
+            Par P1 = parent_view(C, ns, len);
             const bool wd = len >= kWideMin && !K.deg_check;
-            const uint64_t chunks = __ballot(wd && P1.rows_only && P1.n_rows > 0 && P1.len > 0);
-            uint64_t wide = __ballot(wd && P1.len > 0) & ~chunks;
+            const bool rows = wd && P1.rows_only && P1.n_rows > 0 && P1.len > 0;
+            uint64_t wide = __ballot(wd && P1.len > 0 && !rows);
+            Dense dn{};
+            if (rows) dn = take_dense(C, K, nb, brow, bskip, P1);
+            const uint64_t words = __ballot(dn.w1 > dn.w0), chunks = __ballot(rows && P1.len > 0);
             if (wd) len = 0;
             const uint32_t incl = scan_incl(len, lane);
             C.s.incl[lane] = incl;
@@ -994,6 +1152,11 @@ __device__ __forceinline__ void leaf_masks(Ctx& C, uint32_t nb, uint32_t p, bool
                 const uint64_t ba = __ballot(oka), bb = __ballot(okb);
                 if (owns) h += own_count(ba, start, len, t0) + own_count(bb, start, len, t0 + 64);
             }
+            if (words)
+                word_scan(C, P1, dn, K.gt != 0, words, [&](uint32_t j, uint32_t v) {
+                    const uint32_t n = uni(__shfl(scan_incl(v, lane), 63, 64));
+                    h += lane == j ? n : 0u;
+                });
             if (chunks) chunk_scan(C, P1, chunks, [&](uint32_t j, uint32_t n) { h += lane == j ? n : 0u; });
             for (; wide; wide &= wide - 1) {
                 const uint32_t j = (uint32_t)__builtin_ctzll(wide);
@@ -1118,7 +1281,8 @@ __device__ __forceinline__ void count_leaves(Ctx& C, uint32_t lv, uint32_t npref
         {
             // one leaf signature
             const LK& S = S0;
-            uint32_t len = phase_a<true>(C, S, nb, p, pv, false);
+            uint32_t brow, bskip;
+            uint32_t len = phase_a<true>(C, S, nb, p, pv, false, brow, bskip);
             // one leaf whose set is a base list and one probe list: balanced big
             // pairs leave the flattened pass for the cooperative merge
             uint32_t probe_c = kSkip;
@@ -1139,10 +1303,13 @@ __device__ __forceinline__ void count_leaves(Ctx& C, uint32_t lv, uint32_t npref
             }
             uint64_t bigmask = __ballot(big);
             // other long base lists are scanned one by one (listing stays flattened)
-            const Par P1 = parent_view(C, ns, len);
+            Par P1 = parent_view(C, ns, len);
             const bool wd = len >= kWideMin && !big && !listing && !S.deg_check;
-            const uint64_t chunks = __ballot(wd && P1.rows_only && P1.n_rows > 0 && P1.len > 0);
-            uint64_t wide = __ballot(wd && P1.len > 0) & ~chunks;
+            const bool rows = wd && P1.rows_only && P1.n_rows > 0 && P1.len > 0;
+            uint64_t wide = __ballot(wd && P1.len > 0 && !rows);
+            Dense dn{};
+            if (rows) dn = take_dense(C, S, nb, brow, bskip, P1);
+            const uint64_t words = __ballot(dn.w1 > dn.w0), chunks = __ballot(rows && P1.len > 0);
             if (big || wd) len = 0;
             (void)nsig;
             const uint32_t incl = scan_incl(len, lane);
@@ -1172,6 +1339,10 @@ __device__ __forceinline__ void count_leaves(Ctx& C, uint32_t lv, uint32_t npref
                 lin += (unsigned long long)(__popcll(ma) + __popcll(mb));
                 if (listing) write_rows(C, nb, ma, mb, ja, xa, oka, jb, xb, okb);
             }
+            uint32_t vacc = 0;  // this lane's share of the word scans
+            if (words) word_scan(C, P1, dn, S.gt != 0, words, [&](uint32_t, uint32_t v) { vacc += v; });
+            // (64 lists of the largest size stay below 2^32 elements)
+            if (words) lin += uni(__shfl(scan_incl(vacc, lane), 63, 64));
             if (chunks) chunk_scan(C, P1, chunks, [&](uint32_t, uint32_t n) { lin += n; });
             for (; wide; wide &= wide - 1)
                 lin += wide_count(C, S, nb, ns, (uint32_t)__builtin_ctzll(wide));
@@ -1743,11 +1914,38 @@ __global__ void rows_kernel(DevGraph g, const uint32_t* row_node, uint32_t n_out
     }
 }
 
+// Head of each row where words beat elements: the number of words w (a power
+// of two times 256, or the whole row) with the largest kDenseWords x elements - w.
+__global__ void row_pre_kernel(DevGraph g, const uint32_t* row_node, uint32_t n_out_rows, uint32_t n_rows, uint2* pre) {
+    const uint32_t r = blockIdx.x * blockDim.x + threadIdx.x;
+    if (r >= n_rows) return;
+    const uint32_t dir = r >= n_out_rows ? 1u : 0u, v = row_node[r];
+    const uint32_t* off = off_of(g, dir);
+    const uint32_t o = off[v], len = off[v + 1] - o;
+    const uint32_t* list = adj_of(g, dir) + o;
+    const uint32_t whole = g.row_words / 4 * 4;
+    uint2 best = make_uint2(0, 0);
+    int64_t gain = 0;
+    for (uint64_t w = 256; whole > 0; w *= 2) {
+        const uint32_t words = w < whole ? (uint32_t)w : whole;
+        const uint32_t n = count_le(list, len, words * 32u - 1u);
+        const int64_t gn = (int64_t)kDenseWords * n - words;
+        if (gn > gain) {
+            gain = gn;
+            best = make_uint2(words, n);
+        }
+        if (w >= whole) break;
+    }
+    pre[r] = best;
+}
+
 hipError_t build_rows(const DevGraph& g, const uint32_t* row_node, uint32_t n_out_rows, uint32_t n_rows,
-                      uint32_t* rows, hipStream_t stream) {
+                      uint32_t* rows, uint2* row_pre, hipStream_t stream) {
     if (n_rows == 0) return hipSuccess;
     uint32_t blocks = n_rows < 65535u ? n_rows : 65535u;
     hipLaunchKernelGGL(rows_kernel, dim3(blocks), dim3(256), 0, stream, g, row_node, n_out_rows, n_rows, rows);
+    hipLaunchKernelGGL(row_pre_kernel, dim3((n_rows + 255) / 256), dim3(256), 0, stream, g, row_node, n_out_rows,
+                       n_rows, row_pre);
     return hipGetLastError();
 }
 

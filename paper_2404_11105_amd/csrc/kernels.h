@@ -80,6 +80,7 @@ struct DevGraph {
     // rows), bit x set iff node x is in the list
     const uint32_t* rows;
     const uint2* row_of;  // per node: (out row, in row), 0xFFFFFFFF = no row
+    const uint2* row_pre;  // per row: (words, elements) of its dense head
     uint32_t row_words;
     uint32_t pad;
 };
@@ -90,9 +91,9 @@ constexpr uint32_t kRowLen = 0xFFFFFFFEu;  // probe-list length marker: test a d
 constexpr uint64_t kMaxRowBytes = 256ull << 30;  // rows budget, at most (row ids are 32-bit)
 
 // Set the bits of dense rows [0, n_rows): row r holds the out-list (r <
-// n_out_rows) or in-list of node row_node[r].  Rows must be zeroed first.
+// n_out_rows) or in-list of node row_node[r] (rows must be zeroed first), and fill row_pre[r].
 hipError_t build_rows(const DevGraph& g, const uint32_t* row_node, uint32_t n_out_rows, uint32_t n_rows,
-                      uint32_t* rows, hipStream_t stream);
+                      uint32_t* rows, uint2* row_pre, hipStream_t stream);
 
 struct KArgs {
     DevGraph g;

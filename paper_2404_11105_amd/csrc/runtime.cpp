@@ -39,6 +39,7 @@ struct xm_graph_s {
     // dense membership rows of long lists (xm_graph_dense_rows)
     uint32_t* rows = nullptr;       // device, owned: out rows, then in rows
     uint2* row_of = nullptr;        // device, owned: per node (out row, in row)
+    uint2* row_pre = nullptr;       // device, owned: per row (words, elements) of its dense head
     uint32_t row_min = xm::kNoRows, n_rows_out = 0, n_rows_in = 0;
     uint64_t row_words = 0;
     mutable std::atomic<int> execs{0};  // captured launches that hold this graph's pointers
@@ -365,6 +366,7 @@ int enqueue_count(const xm_graph_t* g, uint32_t n_plans, const xm_plan_t* const*
     a.g.row_min = g->rows ? g->row_min : xm::kNoRows;
     a.g.rows = g->rows;
     a.g.row_of = g->row_of;
+    a.g.row_pre = g->row_pre;
     a.g.row_words = (uint32_t)g->row_words;
     a.plans = reinterpret_cast<const PlanDesc*>(base + L.off_table);
     a.n_plans = n_plans;
@@ -749,6 +751,7 @@ int xm_free_graph(xm_graph_t* g) {
     if (g->hubs) (void)hipFree(g->hubs);
     if (g->rows) (void)hipFree(g->rows);
     if (g->row_of) (void)hipFree(g->row_of);
+    if (g->row_pre) (void)hipFree(g->row_pre);
     delete g;
     return XM_OK;
 }
@@ -766,8 +769,10 @@ int xm_graph_dense_rows(xm_graph_t* g, uint64_t max_bytes, uint32_t min_len, voi
     HIP_TRY(hipDeviceSynchronize(), "hipDeviceSynchronize");
     if (g->rows) (void)hipFree(g->rows);
     if (g->row_of) (void)hipFree(g->row_of);
+    if (g->row_pre) (void)hipFree(g->row_pre);
     g->rows = nullptr;
     g->row_of = nullptr;
+    g->row_pre = nullptr;
     g->row_min = xm::kNoRows;
     g->n_rows_out = g->n_rows_in = 0;
     g->row_words = 0;
@@ -816,11 +821,14 @@ int xm_graph_dense_rows(xm_graph_t* g, uint64_t max_bytes, uint32_t min_len, voi
     hipError_t e;
     if ((e = hipMalloc(&g->rows, (n_out + n_in) * row_bytes)) != hipSuccess ||
         (e = hipMalloc(&g->row_of, (size_t)g->n * sizeof(uint2))) != hipSuccess ||
+        (e = hipMalloc(&g->row_pre, (size_t)(n_out + n_in) * sizeof(uint2))) != hipSuccess ||
         (e = hipMalloc(&rn, row_node.size() * 4)) != hipSuccess) {
         if (g->rows) (void)hipFree(g->rows);
         if (g->row_of) (void)hipFree(g->row_of);
+        if (g->row_pre) (void)hipFree(g->row_pre);
         g->rows = nullptr;
         g->row_of = nullptr;
+        g->row_pre = nullptr;
         return fail(XM_ERR_OOM, "hipMalloc(dense rows)");
     }
     g->row_words = words;
@@ -839,14 +847,16 @@ int xm_graph_dense_rows(xm_graph_t* g, uint64_t max_bytes, uint32_t min_len, voi
                             stream)) != hipSuccess ||
         (e = hipMemcpyAsync(rn, row_node.data(), row_node.size() * 4, hipMemcpyHostToDevice, stream)) !=
             hipSuccess ||
-        (e = xm::build_rows(dg, rn, (uint32_t)n_out, (uint32_t)(n_out + n_in), g->rows, stream)) != hipSuccess ||
+        (e = xm::build_rows(dg, rn, (uint32_t)n_out, (uint32_t)(n_out + n_in), g->rows, g->row_pre, stream)) != hipSuccess ||
         (e = hipStreamSynchronize(stream)) != hipSuccess) {
         (void)hipStreamSynchronize(stream);
         (void)hipFree(rn);
         (void)hipFree(g->rows);
         (void)hipFree(g->row_of);
+        (void)hipFree(g->row_pre);
         g->rows = nullptr;
         g->row_of = nullptr;
+        g->row_pre = nullptr;
         g->row_min = xm::kNoRows;
         g->n_rows_out = g->n_rows_in = 0;
         g->row_words = 0;

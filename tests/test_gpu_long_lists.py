@@ -68,3 +68,36 @@ def test_several_probes_per_parent(xa, rows):
     G = xa.Graph(g, **rows)
     for reduced in (True, False):
         assert xa.count(G, [xa.Plan(p, reduced=reduced, graph=G) for p in pats]) == [oracle.count(g, p) for p in pats]
+
+
+def skewed_graph(seed=11, n=20011):
+    """14 nodes with out- and in-lists of 130 to 4,000 nodes, most at low ids
+    (rows with dense heads of one to three chunks of 256 words, the last words
+    of a row in none), joined to each other, over a sparse background."""
+    rng = np.random.default_rng(seed)
+    src, dst = [], []
+    for i, ln in enumerate([130, 257, 500, 511, 512, 700, 1000, 1500, 2000, 2500, 3000, 3500, 3999, 4000]):
+        for into in (False, True):
+            x = np.unique((n * rng.random(2 * ln) ** (1.0 + 0.5 * (i % 4))).astype(np.int64))
+            x = np.concatenate([rng.choice(x, min(ln, x.size), replace=False), np.arange(n - 3, n)])
+            h = np.full(x.size, i)
+            src.append(x if into else h)
+            dst.append(h if into else x)
+    u, v = np.nonzero(rng.random((14, 14)) < 0.6)
+    e = rng.integers(0, n, (2, 30000))
+    return xmgen.from_arcs(n, np.concatenate(src + [u, e[0]]), np.concatenate(dst + [v, e[1]]))
+
+
+def test_dense_heads(xa):
+    g = skewed_graph()
+    P = xmgen.Pattern
+    pats = [xmgen.named("ffl"), xmgen.named("c3"), P(4, ((0, 1), (0, 2), (1, 2), (0, 3), (1, 3))),
+            P(4, ((0, 1), (1, 0), (0, 2), (2, 1), (3, 0), (1, 3)))]
+    want = [oracle.count(g, p) for p in pats]
+    for rows in (dict(row_min=64), dict(row_min=64, dense_rows=24 * 2504), dict(dense_rows=0)):
+        G = xa.Graph(g, **rows)
+        print("[case]", G.dense_rows_info(), flush=True)
+        for reduced in (True, False):
+            assert xa.count(G, [xa.Plan(p, reduced=reduced, graph=G) for p in pats]) == want
+        sym = [xa.Plan(p, graph=G, symmetry=s, reduced=r) for p in pats for s in ("above", "below") for r in (True, False)]
+        assert xa.count(G, sym) == [w for w in want for _ in range(4)]
