@@ -1510,7 +1510,9 @@ __global__ void __launch_bounds__(kBlockThreads, MINB) count_kernel(KArgs a) {
     Ctx C;
     C.a = &a;
     C.lane = lane_id();
-    const uint32_t wid = threadIdx.x >> 6;
+    // uniform over the wave, stated so: what is addressed from it stays in scalar
+    // registers (roomy kernels 168 -> 142 and 161 -> 133 VGPRs)
+    const uint32_t wid = uni(threadIdx.x >> 6);
     C.s = carve(smem + wid * a.lds_words, a.lds_rows, a.maxc, a.merge_min != 0xFFFFFFFFu);
     const uint64_t gw = (uint64_t)blockIdx.x * kWavesPerBlock + wid;
     C.scr = a.scratch + gw * (uint64_t)a.wave_words;
