@@ -37,7 +37,18 @@ static_assert(sizeof(PlanDesc) % 4 == 0, "plan descriptors are copied in 32-bit 
 constexpr uint32_t kSkip = 0xFFFFFFFFu;
 constexpr uint32_t kIdlePolls = 1u << 13;  // polls a waiting wave makes for donated work
 constexpr uint32_t kNapMax = 128;          // longest pause between two polls, in sleeps of 512 clocks (~27 us)
-constexpr uint32_t kDonateAfter = 256;     // windows a task runs before it may donate
+// Work donation: clocks a task runs before it looks whether other waves wait,
+// and between such looks (~0.4 ms); partial matches of one parent in a donated
+// range, at least; clocks a donated range should take; clocks a task runs
+// before it donates single parents.  The costs are in the control words: a line
+// serves ~70 accesses a us, so looks, donated tasks and waiters have to stay few.
+// A tenth of the roots of R-MAT 16 took, with ranges of 2^18 / 2^20 / 2^21 clocks
+// and 512 waiters, 730 / 60 / - ms, with 256 waiters and 2^21 40 ms, without
+// ranges 48 ms; all idle waves waiting with long pauses 51 ms.
+constexpr uint32_t kDonateClocks = 1u << 20;
+constexpr uint32_t kDonatePiece = 64;
+constexpr uint32_t kDonateWork = 1u << 21;
+constexpr uint32_t kDonateParents = 1u << 22;
 constexpr uint32_t kComplete = 0x80000000u;
 // Base lists at least this long are scanned by the whole wave on their own
 // (wide_scan).  Measured at 32 / 64 / 128: unreduced motifs on R-MAT 16 192 /
@@ -197,7 +208,7 @@ struct Lds {
     uint32_t* slot_lo;   // [maxc][64]: address of the list or of the dense row (low word)
     uint32_t* slot_hi;   // [maxc][64]: (high word)
     uint32_t* hist;      // [64][16]
-    uint32_t* st;        // wave state: cur[8], pofs[8], n[8]
+    uint32_t* st;        // wave state: cur[8], pofs[8], n[8], a donated id range: level, from, to
     uint32_t* mbuf;      // [kMergeChunk]: probe-list chunk of the cooperative merge
 };
 
@@ -246,9 +257,10 @@ struct Ctx {
     uint32_t lane;
     unsigned long long acc_lo, acc_hi;  // per-lane 128-bit partial (leaf groups)
     bool ovf;                           // this lane's partial or a leaf-group term left the 128-bit range
-    bool donated;                       // this wave has handed off work (it then always waits)
+    bool donated;                       // this wave has handed off work since it last saw the queue empty
     bool stop;                          // the cancel flag was seen: leave the task
     uint32_t polls;                     // leaf blocks since the last look at the cancel flag
+    uint32_t begun, looked;             // clock of the task's start, and of its last look for waiting waves
 };
 
 // First-level base list length of root r for plan P (shortest constraint list).
@@ -276,6 +288,11 @@ __device__ __forceinline__ uint32_t count_le(const uint32_t* a, uint32_t n, uint
         }
     }
     return lo;
+}
+
+// Number of entries below x in the sorted array a[0, n).
+__device__ __forceinline__ uint32_t count_lt(const uint32_t* a, uint32_t n, uint32_t x) {
+    return x ? count_le(a, n, x - 1u) : 0u;
 }
 
 // Symmetry breaking: the part of the sorted list a[0, len) that lies above
@@ -914,6 +931,18 @@ __device__ __forceinline__ uint32_t expand(Ctx& C, uint32_t lv) {
     const bool pv = p < nparents;
     uint32_t brow, bskip;
     uint32_t len = phase_a<false>(C, D, lv, p, pv, true, brow, bskip);
+    bool cut = false;
+    if (uni(st[24]) == lv && uni(st[26]) != kSkip && pv) {
+        // a donated id range: its part of the sorted base list
+        const uint32_t* base = reinterpret_cast<const uint32_t*>(((uint64_t)C.s.base_hi[lane] << 32) | C.s.base_lo[lane]);
+        const uint32_t lo = count_lt(base, len, uni(st[25])), hi = count_lt(base, len, uni(st[26]));
+        const uint64_t bv = reinterpret_cast<uint64_t>(base + lo);
+        cut = hi - lo < len;
+        len = hi - lo;
+        C.s.base_lo[lane] = (uint32_t)bv;
+        C.s.base_hi[lane] = (uint32_t)(bv >> 32);
+        C.s.base_len[lane] = len;
+    }
     if (pv && lane == 0) len -= pofs;
     uint32_t incl = scan_incl(len, lane);
     C.s.incl[lane] = incl;
@@ -1005,7 +1034,7 @@ __device__ __forceinline__ uint32_t expand(Ctx& C, uint32_t lv) {
         uint32_t ex = scan_incl(cnt, lane) - cnt;
         if (lane < np) {
             Lvl Fi = lvl_arrays(C.scr, cap, lv - 1);
-            bool complete = !(lane == 0 && (pofs > 0 || partial));
+            bool complete = !(lane == 0 && (pofs > 0 || partial)) && !cut;
             if (lv == 1) {
                 // a root split into first-level sub-ranges never has all its children here
                 Lvl F0 = lvl_arrays(C.scr, cap, 0);
@@ -1219,6 +1248,144 @@ __device__ __forceinline__ void write_rows(const Ctx& C, uint32_t nb, uint64_t m
     if (okb) put(base + na + rank_below(mb), jb, xb);
 }
 
+// Whether a task that has run for a while should look for waiting waves now.
+__device__ __forceinline__ bool time_to_look(Ctx& C) {
+    const uint32_t now = (uint32_t)__builtin_readcyclecounter();
+    if (now - C.looked < kDonateClocks) return false;
+    C.looked = now;
+    return true;
+}
+
+// Work donation.  While some waves are idle (all queues drained), a wave that
+// has spent at least kDonateClocks in one task hands off unstarted work as
+// donated tasks, each a prefix phi(v_0..v_{l-1}) with a range of ids at level
+// l, which another wave explores from level l.  It looks at the clock, not at
+// windows done: the leaf pass of one window over hub lists can take
+// milliseconds.  (Donating after 256 windows, and never within a leaf pass,
+// left the ends of launches to a few waves.  Measured then and now: a tenth of
+// the roots of R-MAT 16 48 and 39 ms, C5 + chord on R-MAT 20 73 and 68, TT4 +
+// pendant on R-MAT 18 98-128 and 98-99.)  Slots are reserved with a CAS on the tail (never past
+// the capacity) and published with a ready word.
+// The queue is kept about as long as there are waiting waves: a backlog beyond
+// that only adds tasks that are explored less efficiently than in a full window
+// (with no such bound every running wave donated half of its work each time,
+// 260,000 tasks a launch, and taking them took seconds).
+//
+// Slots that may be donated now (0: none); `tail` becomes the queue's tail.
+__device__ __forceinline__ uint32_t donation_room(const Ctx& C, uint32_t& tail) {
+    uint32_t v = 0;
+    if (C.lane == 0) v = __atomic_load_n(&C.a->ctl[kCtlIdle], __ATOMIC_RELAXED);
+    const uint32_t idle = uni(__shfl(v, 0, 64));
+    tail = 0;
+    if (idle == 0) return 0;
+    if (C.lane < 2) v = __atomic_load_n(&C.a->ctl[C.lane ? kCtlDonTail : kCtlDonHead], __ATOMIC_RELAXED);
+    tail = uni(__shfl(v, 1, 64));
+    const uint32_t head = uni(__shfl(v, 0, 64));
+    return idle > tail - head ? idle - (tail - head) : 0u;
+}
+// Reserve k slots behind the tail that donation_room saw.  One try: thousands of
+// waves may look at the same time, and retrying against each other took longer
+// than the work they had (a failed try comes back with the next look).
+__device__ __forceinline__ uint32_t reserve_slots(Ctx& C, uint32_t k, uint32_t tail) {
+    const KArgs& a = *C.a;
+    uint32_t base = kSkip;
+    if (C.lane == 0 && tail + k <= a.don_cap && atomicCAS(&a.ctl[kCtlDonTail], tail, tail + k) == tail) base = tail;
+    base = uni(__shfl(base, 0, 64));
+    if (base != kSkip) C.donated = true;
+    return base;
+}
+// One donated task: level l below entry idx of level l-1, ids in [xlo, xhi).
+__device__ __forceinline__ void donate(Ctx& C, uint32_t slot, uint32_t l, uint32_t idx, uint32_t xlo, uint32_t xhi) {
+    const KArgs& a = *C.a;
+    uint32_t* ent = a.don + (uint64_t)slot * kDonWords;
+    // Relaxed atomics go past the XCD's L2 by themselves; a release fence would
+    // write that whole L2 back and the taker's acquire would empty its own (a
+    // launch with 50,000 donated tasks spent most of a second on it).  The
+    // entry's words have arrived once the stores are counted back.
+    auto put = [&](uint32_t w, uint32_t v) { __atomic_store_n(&ent[w], v, __ATOMIC_RELAXED); };
+    for (int j = (int)l - 1; j >= 0; --j) {
+        Lvl F = lvl_arrays(C.scr, a.cap, (uint32_t)j);
+        put(2 + (uint32_t)j, F.node[idx]);
+        if (j > 0) idx = F.parent[idx];
+    }
+    put(kDonWords - 2, xlo);
+    put(kDonWords - 1, xhi);
+    put(0, C.pi | (l << 16));
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    put(1, 1u);
+}
+
+// At the shallowest level l >= 2 with at least two parents at level l-1 not yet
+// expanded, the last half of them (at most 64) become donated tasks; the donor
+// drops them from its window.
+__device__ __forceinline__ void donate_parents(Ctx& C, uint32_t start, uint32_t lv) {
+    uint32_t* st = C.s.st;
+    uint32_t tail;
+    const uint32_t room = donation_room(C, tail);
+    if (room == 0) return;
+    for (uint32_t l = (start > 2 ? start : 2); l <= lv; l++) {
+        const uint32_t n = uni(st[16 + l - 1]);
+        uint32_t first = uni(st[l]);
+        if (l == lv && uni(st[8 + l]) > 0) first += 1;  // a parent in the middle of a slice stays
+        if (first >= n || n - first < 2) continue;
+        uint32_t k = (n - first) / 2;
+        k = k < 64 ? k : 64;
+        k = k < room ? k : room;
+        const uint32_t base = reserve_slots(C, k, tail);
+        if (base == kSkip) return;  // no room: keep the work
+        if (C.lane < k) donate(C, base + C.lane, l, n - k + C.lane, 0, kSkip);
+        if (C.lane == 0) st[16 + l - 1] = n - k;
+        wave_sync();
+        return;
+    }
+}
+
+// Within the leaf pass over level lv's window: donate about the last half of
+// the partial matches [from, n) that are not counted yet, as id ranges below
+// their parents (level lv is expanded again there, for these ids only).
+// each: clocks a partial match took so far; a range should take kDonateWork.
+// Returns the new end of the window.
+__device__ __forceinline__ uint32_t donate_leaves(Ctx& C, uint32_t lv, uint32_t from, uint32_t n, uint32_t each) {
+    if (n < from + 2 * kDonatePiece) return n;
+    const uint64_t pieces = (uint64_t)each * ((n - from) / 2) / kDonateWork;
+    if (pieces == 0) return n;
+    uint32_t tail;
+    uint32_t room = donation_room(C, tail);
+    if (room == 0) return n;
+    room = room < 64 ? room : 64;
+    room = room < pieces ? room : (uint32_t)pieces;
+    const KArgs& a = *C.a;
+    const uint32_t lane = C.lane;
+    Lvl F = lvl_arrays(C.scr, a.cap, lv);
+    const uint32_t s = from + (n - from) / 2;
+    const uint32_t pl = uni(F.parent[s]), ph = uni(F.parent[n - 1]);
+    uint32_t q = ph, b = n, e = n;
+    if (pl == ph) {
+        // one parent: pieces of its children
+        uint32_t sz = (n - s + room - 1) / room;
+        sz = sz < kDonatePiece ? kDonatePiece : sz;
+        b = s + lane * sz;
+        e = b + sz;
+        b = b < n ? b : n;
+        e = e < n ? e : n;
+    } else {
+        // the children of each of the last parents, at most 64 of them
+        const uint32_t np = ph - pl < room ? ph - pl : room;
+        if (lane < np) {
+            q = ph - np + 1 + lane;
+            b = count_lt(F.parent, n, q);
+            e = count_lt(F.parent, n, q + 1);
+        }
+    }
+    const uint64_t m = __ballot(b < e);
+    if (!m) return n;
+    const uint32_t base = reserve_slots(C, (uint32_t)__popcll(m), tail);
+    if (base == kSkip) return n;
+    if (b < e) donate(C, base + rank_below(m), lv, q, F.node[b], F.node[e - 1] + 1u);
+    wave_sync();
+    return uni(__shfl(b, (int)__builtin_ctzll(m), 64));
+}
+
 // Count the leaf group for every partial match in level `lv` (= e - 1).
 template <bool NONLIN>
 __device__ __forceinline__ void count_leaves(Ctx& C, uint32_t lv, uint32_t nprefix) {
@@ -1229,6 +1396,7 @@ __device__ __forceinline__ void count_leaves(Ctx& C, uint32_t lv, uint32_t npref
     const bool linear = !NONLIN || P->linear != 0;
     const uint32_t nb = lv + 1;  // bound levels 0..lv
     const LK S0 = load_lk(P->sig[0], a);
+    const uint32_t entered = (uint32_t)__builtin_readcyclecounter();
     for (uint32_t w0 = 0; w0 < nprefix; w0 += 64) {
         // a leaf pass over hub lists can run long: look at the cancel flag
         // every 8 blocks of 64 prefixes
@@ -1241,6 +1409,8 @@ __device__ __forceinline__ void count_leaves(Ctx& C, uint32_t lv, uint32_t npref
                 return;
             }
         }
+        if (lv > 0 && w0 > 0 && time_to_look(C))
+            nprefix = donate_leaves(C, lv, w0 + 64, nprefix, (C.looked - entered) / w0);
         const uint32_t p = w0 + lane;
         const bool pv = p < nprefix;
         // walk the chain once: bound nodes of levels 0..lv
@@ -1392,62 +1562,6 @@ __device__ __forceinline__ void flush(Ctx& C) {
     C.ovf = false;
 }
 
-// Work donation.  While some waves are idle (all queues drained), a wave that
-// has spent at least kDonateAfter windows in one task (a straggler: most tasks
-// take a few windows, and a donated subtree is explored less efficiently than
-// in a full window) hands off unstarted partial matches: at the shallowest
-// level l >= 2 with at least two parents at level l-1 not yet expanded, the
-// last half of them (at most 64) become donated tasks, each carrying its
-// prefix phi(v_0..v_{l-1}); the donor drops them from its window.  A donated
-// task is explored from level l by another wave.  Slots are reserved with a
-// CAS on the tail (never past the capacity) and published with a ready flag.
-__device__ __forceinline__ void maybe_donate(Ctx& C, uint32_t start, uint32_t lv) {
-    const KArgs& a = *C.a;
-    uint32_t* st = C.s.st;
-    uint32_t idle = 0;
-    if (C.lane == 0) idle = __atomic_load_n(&a.ctl[kCtlIdle], __ATOMIC_RELAXED);
-    if (uni(__shfl(idle, 0, 64)) == 0) return;
-    for (uint32_t l = (start > 2 ? start : 2); l <= lv; l++) {
-        const uint32_t n = uni(st[16 + l - 1]);
-        uint32_t first = uni(st[l]);
-        if (l == lv && uni(st[8 + l]) > 0) first += 1;  // a parent in the middle of a slice stays
-        if (first >= n || n - first < 2) continue;
-        uint32_t k = (n - first) / 2;
-        k = k < 64 ? k : 64;
-        // reserve k slots
-        uint32_t base = kSkip;
-        if (C.lane == 0) {
-            uint32_t t = __atomic_load_n(&a.ctl[kCtlDonTail], __ATOMIC_RELAXED);
-            while (t + k <= a.don_cap) {
-                const uint32_t seen = atomicCAS(&a.ctl[kCtlDonTail], t, t + k);
-                if (seen == t) {
-                    base = t;
-                    break;
-                }
-                t = seen;
-            }
-        }
-        base = uni(__shfl(base, 0, 64));
-        if (base == kSkip) return;  // no room: keep the work
-        C.donated = true;
-        if (C.lane < k) {
-            uint32_t* ent = a.don + (uint64_t)(base + C.lane) * kDonWords;
-            uint32_t idx = n - k + C.lane;
-            for (int j = (int)l - 1; j >= 0; --j) {
-                Lvl F = lvl_arrays(C.scr, a.cap, (uint32_t)j);
-                ent[2 + j] = F.node[idx];
-                if (j > 0) idx = F.parent[idx];
-            }
-            ent[0] = C.pi | (l << 16);
-            __threadfence();
-            __atomic_store_n(&ent[1], 1u, __ATOMIC_RELEASE);
-        }
-        if (C.lane == 0) st[16 + l - 1] = n - k;
-        wave_sync();
-        return;
-    }
-}
-
 // Depth-first exploration of the n0 partial matches held in level start-1
 // (start = 1: roots in level 0).
 template <bool NONLIN>
@@ -1464,6 +1578,7 @@ __device__ __forceinline__ void explore(Ctx& C, uint32_t n0, uint32_t start) {
         st[8 + start] = 0;
     }
     wave_sync();
+    C.begun = C.looked = (uint32_t)__builtin_readcyclecounter();
     uint32_t lv = start;
     uint32_t windows = 0;
     for (;;) {
@@ -1484,7 +1599,7 @@ __device__ __forceinline__ void explore(Ctx& C, uint32_t n0, uint32_t start) {
                 break;
             }
         }
-        if (windows >= kDonateAfter && (windows & 7u) == 0 && lv >= 2) maybe_donate(C, start, lv);
+        if (lv >= 2 && time_to_look(C) && C.looked - C.begun >= kDonateParents) donate_parents(C, start, lv);
         uint32_t nout = expand(C, lv);
         if (lv == e - 1) {
             if (nout) count_leaves<NONLIN>(C, lv, nout);
@@ -1523,6 +1638,7 @@ __global__ void __launch_bounds__(kBlockThreads, MINB) count_kernel(KArgs a) {
     C.donated = false;
     C.stop = false;
     C.polls = 0;
+    C.begun = C.looked = 0;
     // this wave's home split queue: the XCD its block runs on (blocks go to
     // the 8 XCDs round-robin), so a hub's sub-range tasks share one L2
     const uint32_t home = blockIdx.x % kQueues;
@@ -1632,40 +1748,61 @@ __global__ void __launch_bounds__(kBlockThreads, MINB) count_kernel(KArgs a) {
         }
         if (kind == 2 && !stop) {
             // queues drained: wait for donated work while any wave still holds a
-            // task.  At most kMaxWaiters waves wait (the others leave at once),
-            // and they poll with growing pauses, so waiting waves do not crowd
-            // the cache lines the working waves update.
-            // A wave that donated always waits: a waiter that read the queue
-            // just before a donation was published and the active count just
-            // after its donor finished would leave without it, and the donor
-            // itself then takes its entries (the poll checks the queue first).
-            bool wait = C.donated;
+            // task.  About kMaxWaiters waves wait (the others leave at once), and
+            // they poll with growing pauses, so waiting waves do not crowd the
+            // cache lines the working waves update.
+            // A wave that donated leaves only after it has seen the queue empty
+            // (every entry claimed), whatever the number of waiters: so none of
+            // its entries is lost when the waiters have gone.
             uint32_t idle = 0;
             if (ln == 0) idle = __atomic_load_n(&a.ctl[kCtlIdle], __ATOMIC_RELAXED);
-            wait = wait || uni(__shfl(idle, 0, 64)) < kMaxWaiters;
-            if (wait) {
+            const bool wait = uni(__shfl(idle, 0, 64)) < kMaxWaiters;
+            if (wait || C.donated) {
                 // between the read and this add a few more waves than
                 // kMaxWaiters may come in; they may wait as well
-                if (ln == 0) atomicAdd(&a.ctl[kCtlIdle], 1u);
+                if (wait && ln == 0) atomicAdd(&a.ctl[kCtlIdle], 1u);
                 uint32_t nap = 1;
                 for (uint32_t polls = 0; polls < kIdlePolls; polls++) {
-                    uint32_t h = 0, t = 0;
+                    // queue entries [head, tail): ready words 0 reserved, 1 published,
+                    // 2 claimed.  A waiter tries an entry of its own choosing, so
+                    // the claims spread over the entries (one CAS on the head by
+                    // all waiters took ~7 us a task); now and then it is the head,
+                    // which moves past claimed entries.
+                    uint32_t h = 0, t = 0, got = kSkip;
                     if (ln == 0) {
                         h = __atomic_load_n(&a.ctl[kCtlDonHead], __ATOMIC_RELAXED);
                         t = __atomic_load_n(&a.ctl[kCtlDonTail], __ATOMIC_RELAXED);
+                        if (h < t) {
+                            const uint32_t r = (uint32_t)(gw * 2654435761u + polls * 40503u) >> 9;
+                            const uint32_t s = (r & 3u) ? h + r % (t - h) : h;
+                            uint32_t* const word = &a.don[(uint64_t)s * kDonWords + 1];
+                            const uint32_t seen = __atomic_load_n(word, __ATOMIC_RELAXED);
+                            if (seen == 1u && atomicCAS(word, 1u, 2u) == 1u) got = s;
+                            // move the head past claimed entries
+                            for (uint32_t i = 0; s == h && h < t && i < 8; i++) {
+                                if (__atomic_load_n(&a.don[(uint64_t)h * kDonWords + 1], __ATOMIC_RELAXED) != 2u) break;
+                                atomicCAS(&a.ctl[kCtlDonHead], h, h + 1);
+                                h++;
+                            }
+                        }
                     }
+                    got = uni(__shfl(got, 0, 64));
                     h = uni(__shfl(h, 0, 64));
                     t = uni(__shfl(t, 0, 64));
+                    if (got != kSkip) {
+                        kind = 3;
+                        item = got;
+                        break;
+                    }
+                    // a line of control words serves ~70 accesses a us: hundreds of
+                    // waiters that look at once slow every other update down
                     if (h < t) {
-                        uint32_t got = 0;
-                        if (ln == 0) got = atomicCAS(&a.ctl[kCtlDonHead], h, h + 1) == h;
-                        if (uni(__shfl(got, 0, 64))) {
-                            kind = 3;
-                            item = h;
-                            break;
-                        }
+                        for (uint32_t z = 0; z < nap; z++) __builtin_amdgcn_s_sleep(8);
+                        nap = nap < kNapMax ? nap * 2 : kNapMax;
                         continue;
                     }
+                    C.donated = false;
+                    if (!wait) break;
                     uint32_t act = 0;
                     if (ln < kActiveLines)
                         act = __atomic_load_n(&a.ctl[kCtlActive0 + 32 * ln], __ATOMIC_RELAXED);
@@ -1680,7 +1817,7 @@ __global__ void __launch_bounds__(kBlockThreads, MINB) count_kernel(KArgs a) {
                     for (uint32_t z = 0; z < nap; z++) __builtin_amdgcn_s_sleep(8);
                     nap = nap < kNapMax ? nap * 2 : kNapMax;
                 }
-                if (ln == 0) atomicSub(&a.ctl[kCtlIdle], 1u);
+                if (wait && ln == 0) atomicSub(&a.ctl[kCtlIdle], 1u);
             }
         }
         if (kind == 3) {
@@ -1708,30 +1845,25 @@ __global__ void __launch_bounds__(kBlockThreads, MINB) count_kernel(KArgs a) {
             }
             n0 = 1;
         } else if (kind == 3) {
-            // a donated prefix: bind levels 0..d-1 as single entries and explore from level d
+            // a donated prefix: bind levels 0..d-1 as single entries and explore from
+            // level d, within the id range that came with it
             uint32_t* ent = a.don + (uint64_t)item * kDonWords;
-            uint32_t ready = 0;
-            if (C.lane == 0) {
-                for (uint32_t spin = 0; spin < kIdlePolls; spin++) {
-                    ready = __atomic_load_n(&ent[1], __ATOMIC_ACQUIRE);
-                    if (ready) break;
-                    __builtin_amdgcn_s_sleep(1);
-                }
-                if (!ready) atomicOr(&a.ctl[kCtlBadPlan], 1u);  // a reserved slot never published
-            }
-            ready = uni(__shfl(ready, 0, 64));
-            __atomic_thread_fence(__ATOMIC_ACQUIRE);  // every lane reads the entry after its ready flag
-            const uint32_t head = ready ? uni(__atomic_load_n(&ent[0], __ATOMIC_RELAXED)) : (1u << 16);
+            asm volatile("" ::: "memory");  // (its words are read past L2, after the claim)
+            const uint32_t head = uni(__atomic_load_n(&ent[0], __ATOMIC_RELAXED));
             set_plan(head & 0xFFFFu);
             start = head >> 16;
-            if (ready && C.lane < start) {
+            if (C.lane < start) {
                 Lvl F = lvl_arrays(C.scr, a.cap, C.lane);
                 F.node[0] = __atomic_load_n(&ent[2 + C.lane], __ATOMIC_RELAXED);
                 F.parent[0] = 0;
                 F.segc[0] = 0;  // no complete child segments: reusers fetch their lists
                 F.aux[0] = kSkip;
             }
-            n0 = ready ? 1u : 0u;
+            if (C.lane == 0) {
+                C.s.st[25] = __atomic_load_n(&ent[kDonWords - 2], __ATOMIC_RELAXED);
+                C.s.st[26] = __atomic_load_n(&ent[kDonWords - 1], __ATOMIC_RELAXED);
+            }
+            n0 = 1;
         } else {
             // interleave plans so that all of them start on the low (hub) ids
             set_plan(uni(item % a.n_plans));
@@ -1772,6 +1904,7 @@ __global__ void __launch_bounds__(kBlockThreads, MINB) count_kernel(KArgs a) {
             }
             n0 = (uint32_t)__popcll(m);
         }
+        if (C.lane == 0) C.s.st[24] = kind == 3 ? start : 0u;
         wave_sync();
         if (n0) explore<NONLIN>(C, n0, start);
         if (C.stop) break;

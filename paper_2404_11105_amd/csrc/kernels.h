@@ -19,10 +19,11 @@ constexpr uint32_t kMergeRatio = 16;  // ... and within this length ratio -> mer
 // Control words at the start of the workspace.
 constexpr uint32_t kQueues = 8;  // split-task queues, one per XCD (8 XCDs on MI355X)
 constexpr uint32_t kActiveLines = 64;  // one per lane of a waiting wave
-constexpr uint32_t kMaxWaiters = 512;  // waves that wait for donated work; the others leave
-constexpr uint32_t kDonWords = 8;  // donated task: plan | depth << 16, ready flag, prefix nodes [6]
+constexpr uint32_t kMaxWaiters = 256;  // waves that wait for donated work; the others leave
+constexpr uint32_t kDonWords = 9;  // donated task: plan | depth << 16, ready flag, prefix nodes [5], id range [2]
+static_assert(kMaxK - 1 <= 6, "a donated prefix has at most 5 nodes (levels 0..e-2, e <= 6)");
 constexpr uint32_t kDonCap = 1u << 18;  // donated-task slots per launch
-constexpr uint32_t kDonCapStatic = (1u << 14) - (1u << 11);  // ... in launches on the static scratch array
+constexpr uint32_t kDonCapStatic = 3u << 12;  // ... in launches on the static scratch array
 // Copies of the count totals: 32 for up to 64 plans, then fewer (plans spread
 // the updates by themselves); a copy starts on a cache line of its own.
 inline uint32_t count_copies(uint32_t n_plans) {

@@ -101,3 +101,20 @@ def test_dense_heads(xa):
             assert xa.count(G, [xa.Plan(p, reduced=reduced, graph=G) for p in pats]) == want
         sym = [xa.Plan(p, graph=G, symmetry=s, reduced=r) for p in pats for s in ("above", "below") for r in (True, False)]
         assert xa.count(G, sym) == [w for w in want for _ in range(4)]
+
+
+@pytest.mark.parametrize("reduced", [True, False])
+def test_one_heavy_root_is_shared_out(xa, reduced):
+    """One hub root whose whole work is a single task (its first-level list is
+    not split): other waves get parts of its windows, as single parents and as
+    id ranges below one parent, and the counts stay the root's."""
+    g = xmgen.rmat(13, seed=3)
+    hub = np.array([int(np.argmax(g.out_deg() + g.in_deg()))], dtype=np.uint32)
+    G = xa.Graph(g)
+    for name in ("ffl", "c4", "bifan"):
+        p = xmgen.named(name)
+        plan = xa.Plan(p, reduced=reduced, graph=G, root_vertex=0)
+        want = oracle.count(g, p, roots=hub, root_vertex=0)
+        for opts in (dict(split=4096, split_work=1 << 30), dict(split=4096, split_work=1 << 30, cap=4096, chunk=1)):
+            print("[case]", name, reduced, opts, flush=True)
+            assert xa.count(G, [plan], roots=hub, **opts) == [want]
