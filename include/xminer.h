@@ -275,7 +275,8 @@ typedef struct xm_count_opts {
                                at least split) */
     uint32_t waves_per_cu;  /* resident waves per compute unit, 4..32 (default:
                                as many as LDS allows, at most 32; when that is
-                               fewer than 24, 12 or as many as LDS allows).
+                               fewer than 24, or no list of the graph has more
+                               than 64 elements, 12 or as many as LDS allows).
                                Launches of at most 12 waves per CU run a build
                                of the count kernel that keeps all its state in
                                registers; larger ones a build limited to 64
@@ -298,7 +299,8 @@ typedef struct xm_count_opts {
     /* single-leaf intersections whose two lists are both at least merge_min
        long (default 0xFFFFFFFF: off) and within merge_ratio of each
        other (default 16) are counted by a wave-cooperative merge instead of
-       per-element binary search. */
+       per-element binary search (in launches whose plans all have one
+       leaf). */
     uint32_t merge_min;
     uint32_t merge_ratio;
     /* Profiling (nullable hipEvent_t): recorded on hip_stream immediately

@@ -14,13 +14,15 @@
 // every other constraint list: one bit test when the list is long enough to
 // have a dense row (an n-bit membership row built at graph load, the HBM
 // analogue of staging a hub's list), else a binary search of the sorted
-// uint32 list.  The
-// survivors are compacted with a 64-bit ballot and a popcount.  The leaf
-// group of a plan is counted, not enumerated: with one leaf the count is a
-// popcount sum; with several, each partial match builds a membership
-// histogram in LDS and evaluates the planner's inclusion-exclusion terms in
-// 128-bit integers.  Totals are unsigned 128-bit, kept as (lo, hi) uint64
-// pairs updated with 64-bit atomics and an explicit carry.
+// uint32 list.  The survivors are compacted with a 64-bit ballot and a
+// popcount.  The leaf group of a plan is counted, not enumerated (leaf_set): the
+// heads of long lists' rows word by word (word_scan), the rest of long lists in
+// chunks (chunk_scan), short lists flattened across the window, there against a
+// bit map in LDS of a list that the window shares where it pays (use_filter).
+// One leaf adds the set sizes up; several evaluate the planner's
+// inclusion-exclusion terms over them in 128-bit integers.  Totals are
+// unsigned 128-bit, kept as (lo, hi) uint64 pairs updated with 64-bit atomics
+// and an explicit carry.
 //
 // Nothing here is a dense contraction, so no matrix cores are used; the
 // kernels are bound by memory latency and bandwidth of list reads.
@@ -207,31 +209,33 @@ struct Lds {
     uint32_t* slot_len;  // [maxc][64]: probe k of the parent: list length, kRowLen, or kSkip
     uint32_t* slot_lo;   // [maxc][64]: address of the list or of the dense row (low word)
     uint32_t* slot_hi;   // [maxc][64]: (high word)
-    uint32_t* hist;      // [64][16]
-    uint32_t* st;        // wave state: cur[8], pofs[8], n[8], a donated id range: level, from, to
+    uint32_t* hist;      // [signature masks][64]
+    uint32_t* filt;      // [filt_words]: bit map of a shared list
+    uint32_t* st;        // wave state: cur[8], pofs[8], n[8], a donated id range: level, from, to;
+                         // the filter's list: address (2 words), length
     uint32_t* mbuf;      // [kMergeChunk]: probe-list chunk of the cooperative merge
 };
 
-__device__ __forceinline__ Lds carve(uint32_t* w, uint32_t rows, uint32_t maxc, bool merge) {
+__device__ __forceinline__ Lds carve(uint32_t* w, uint32_t rows, uint32_t maxc, bool merge,
+                                        uint32_t filt_words) {
+    // the arrays of fixed size come first: their addresses are one register
+    // plus constants
     Lds s;
-    s.bound = w;
-    s.anc = w + rows * 64;
-    uint32_t* q = w + 2 * rows * 64;
-    s.base_lo = q;
-    s.base_len = q + 64;
-    s.base_hi = q + 128;
-    s.incl = q + 192;
-    s.segcnt = q + 256;
-    s.mark = q + 320;
-    q += 7 * 64;
-    s.slot_len = q;
-    s.slot_lo = q + maxc * 64;
-    s.slot_hi = q + 2 * maxc * 64;
-    q += 3 * maxc * 64;
-    s.mbuf = q;
-    q += merge ? kMergeChunk : 0;
-    s.st = q;
-    s.hist = q + 32;
+    s.base_lo = w;
+    s.base_len = w + 64;
+    s.base_hi = w + 128;
+    s.incl = w + 192;
+    s.segcnt = w + 256;
+    s.mark = w + 320;
+    s.st = w + 448;
+    s.bound = w + 480;
+    s.anc = s.bound + rows * 64;
+    s.slot_len = s.anc + rows * 64;
+    s.slot_lo = s.slot_len + maxc * 64;
+    s.slot_hi = s.slot_lo + maxc * 64;
+    s.mbuf = s.slot_hi + maxc * 64;
+    s.filt = s.mbuf + (merge ? kMergeChunk : 0);
+    s.hist = s.filt + filt_words;
     return s;
 }
 
@@ -320,16 +324,17 @@ __device__ __forceinline__ void sym_trim(const Lds& s, uint32_t gt, uint32_t lt,
 // the parent chain into LDS (bound nodes, ancestor indices), picks the base
 // list and writes the probes (the other constraint lists, long ones as their
 // dense rows) into the parent's probe slots.  Returns the base length; for a
-// leaf pass brow becomes the dense row of the base list (kSkip: none) and bskip
-// the elements cut off its front.
+// leaf pass brow becomes the dense row of the base list (kSkip: none), bskip
+// the elements cut off its front, and flen the length of the shortest list of a
+// constraint outside `shared` (kSkip: none).
 template <bool IS_SIG>
-__device__ __forceinline__ uint32_t phase_a(Ctx& C, const LK& D, uint32_t lv, uint32_t p, bool pv, bool walk, uint32_t& brow,
-                                            uint32_t& bskip) {
+__device__ __forceinline__ uint32_t phase_a(Ctx& C, const LK& D, uint32_t lv, uint32_t p, bool pv, bool walk,
+                                            uint32_t shared, uint32_t& flen, uint32_t& brow, uint32_t& bskip) {
     const KArgs& a = *C.a;
     const DevGraph& g = a.g;
     const uint32_t lane = C.lane;
     uint32_t len = 0;
-    brow = kSkip;
+    brow = flen = kSkip;
     bskip = 0;
     if (!pv) {
         C.s.base_len[lane] = 0;
@@ -367,6 +372,7 @@ __device__ __forceinline__ uint32_t phase_a(Ctx& C, const LK& D, uint32_t lv, ui
                 const uint32_t* off = off_of(g, D.dir(c));
                 const uint32_t o = off[nd];
                 uint32_t l = off[nd + 1] - o;
+                if (!((shared >> c) & 1u) && l < flen) flen = l;
                 const uint32_t* ptr = probe_ref(g, D.dir(c), nd, o, l);
                 put(k++, ptr, l);
             }
@@ -381,6 +387,7 @@ __device__ __forceinline__ uint32_t phase_a(Ctx& C, const LK& D, uint32_t lv, ui
             const uint32_t nd = C.s.bound[D.lvl(c) * 64 + lane];
             const uint32_t* off = off_of(g, D.dir(c));
             const uint32_t o = off[nd], l = off[nd + 1] - o;
+            if (!((shared >> c) & 1u) && l < flen) flen = l;
             if (l < best) {
                 best = l;
                 bc = c;
@@ -498,14 +505,40 @@ __device__ __forceinline__ bool probe_one(gptr ptr, uint32_t len, uint32_t x) {
     return contains(ptr, len, x);
 }
 
+// A bit map in LDS of one list that the partial matches of a window share (a
+// constraint on a node bound at an earlier level).  Ids below lim have a bit of
+// their own; the others share the map's second half by their low bits and are
+// verified against the list (probe slot vk).  lim = 0xFFFFFFFF: every id of the
+// graph has its own bit.  Lanes (window parents) in `lanes` use it.
+struct Filter {
+    uint64_t lanes;
+    const uint32_t* bits;
+    uint32_t lim, vk;
+    __device__ __forceinline__ bool has(uint32_t x) const {
+        const uint32_t i = x < lim ? x : (lim | (x & (lim - 1u)));
+        return __builtin_amdgcn_ubfe(bits[i >> 5], i, 1u) != 0;
+    }
+};
+
 // Candidate tests of two elements (xa of window parent ja, xb of jb) against
 // level D: injectivity (levels in `inj`), degree thresholds, then each probe
 // slot as a dense-row bit test or a sorted-list search.  oka / okb: in =
 // element valid, out = element passes.
-__device__ __forceinline__ void check_pair(const Ctx& C, const LK& D, uint32_t inj, uint32_t lv, uint32_t ns,
+template <bool FILT>
+__device__ __forceinline__ void check_pair(const Ctx& C, const LK& D, const Filter& flt, uint32_t inj, uint32_t lv, uint32_t ns,
                                            uint32_t ja, uint32_t xa, bool& oka, uint32_t jb, uint32_t xb,
                                            bool& okb) {
     const DevGraph& g = C.a->g;
+    bool fa = false, fb = false;  // the filter decides the probe in slot vk
+    if (FILT && flt.lanes) {
+        fa = (flt.lanes >> ja) & 1u;
+        fb = (flt.lanes >> jb) & 1u;
+        const bool ha = flt.has(xa), hb = flt.has(xb);
+        oka = oka && (ha || !fa);
+        okb = okb && (hb || !fb);
+        fa = fa && xa < flt.lim;
+        fb = fb && xb < flt.lim;
+    }
     for (uint32_t l = 0; l < lv; l++)
         if ((inj >> l) & 1u) {
             oka = oka && (xa != C.s.bound[l * 64 + ja]);
@@ -520,7 +553,11 @@ __device__ __forceinline__ void check_pair(const Ctx& C, const LK& D, uint32_t i
     }
     const gptr safe = (gptr)safe_ptr(g);
     for (uint32_t k = 0; k < ns; k++) {
-        const uint32_t lA = C.s.slot_len[k * 64 + ja], lB = C.s.slot_len[k * 64 + jb];
+        uint32_t lA = C.s.slot_len[k * 64 + ja], lB = C.s.slot_len[k * 64 + jb];
+        if (FILT && k == flt.vk) {
+            lA = fa ? kSkip : lA;
+            lB = fb ? kSkip : lB;
+        }
         const gptr pA = join_ptr(C.s.slot_lo[k * 64 + ja], C.s.slot_hi[k * 64 + ja]);
         const gptr pB = join_ptr(C.s.slot_lo[k * 64 + jb], C.s.slot_hi[k * 64 + jb]);
         const bool rA = oka && lA == kRowLen, rB = okb && lB == kRowLen;
@@ -719,8 +756,12 @@ __device__ __forceinline__ uint32_t from_lane(uint32_t v, uint32_t j) {
 // four row loads outstanding.  Everything about a chunk is scalar, read from
 // its lane's registers: ~6 vector instructions a tile.  Measured against one
 // parent at a time (wide_scan): TT4 + pendant on R-MAT 18 134 and 127 ms (best
-// runs 129 and 103), four motifs on R-MAT 16 21.5 and 20.1, unreduced 158 and 154.
-template <class F>
+// runs 129 and 103), four motifs on R-MAT 16 21.5 and 20.1, unreduced 158 and 154;
+// loading ahead: 96 plans on R-MAT 22 348 and 328, C5 + chord on R-MAT 20 67 and
+// 62, TT4 + pendant on R-MAT 18 99 and 90.
+// AHEAD: the next pair's base loads are issued before the current pair's tests
+// (in the kernels that have the registers for it).
+template <bool AHEAD, class F>
 __device__ __forceinline__ void chunk_scan(const Ctx& C, const Par& P, uint64_t todo, F&& add) {
     struct Chunk {
         gptr base, r0, r1;
@@ -751,18 +792,28 @@ __device__ __forceinline__ void chunk_scan(const Ctx& C, const Par& P, uint64_t 
         c.n = left - i0 < 128u ? left - i0 : 128u;
         i0 += 128;
     };
-    while (todo || i0 < left) {
-        Chunk c[2];
-        next(c[0]);
-        next(c[1]);
-        uint32_t x[4], w[4];
-        uint64_t in[4];
+    Chunk c[2];
+    uint32_t x[4];
+    auto load = [&](Chunk* k, uint32_t* y) {
+        next(k[0]);
+        next(k[1]);
 #pragma unroll
         for (int u = 0; u < 4; u++) {
             // lanes past the end read the last element again
+            const uint32_t n = k[u >> 1].n, i = (u & 1) * 64u + lane, last = n ? n - 1 : 0u;
+            y[u] = k[u >> 1].base[i < last ? i : last];
+        }
+    };
+    if (AHEAD) load(c, x);
+    while (AHEAD ? c[0].n != 0 : (todo || i0 < left)) {
+        Chunk nc[2];
+        uint32_t y[4], w[4];
+        uint64_t in[4];
+        if (AHEAD) load(nc, y);
+        else load(c, x);
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
             const uint32_t n = c[u >> 1].n, off = (u & 1) * 64u;
-            const uint32_t i = off + lane, last = n ? n - 1 : 0u;
-            x[u] = c[u >> 1].base[i < last ? i : last];
             in[u] = n >= off + 64u ? ~0ull : (n > off ? (1ull << (n - off)) - 1ull : 0ull);
         }
 #pragma unroll
@@ -778,6 +829,12 @@ __device__ __forceinline__ void chunk_scan(const Ctx& C, const Par& P, uint64_t 
         }
         add(c[0].j, (uint32_t)(__popcll(in[0]) + __popcll(in[1])));
         add(c[1].j, (uint32_t)(__popcll(in[2]) + __popcll(in[3])));
+        if (AHEAD) {
+            c[0] = nc[0];
+            c[1] = nc[1];
+#pragma unroll
+            for (int u = 0; u < 4; u++) x[u] = y[u];
+        }
     }
 }
 
@@ -917,6 +974,129 @@ __device__ __forceinline__ void word_scan(const Ctx& C, const Par& P, const Dens
     }
 }
 
+// Levels whose bound node is the same for all partial matches of the window
+// (bit l: level l < nb).
+__device__ __forceinline__ uint32_t same_levels(const Ctx& C, uint32_t nb, bool pv) {
+    uint32_t m = 0;
+    for (uint32_t l = 0; l < nb; l++) {
+        const uint32_t v = C.s.bound[l * 64 + C.lane];
+        if (!__ballot(pv && v != uni(v))) m |= 1u << l;  // (lane 0 always holds a partial match)
+    }
+    return m;
+}
+
+// Constraints of D on the levels in `same`.
+__device__ __forceinline__ uint32_t shared_cons(const LK& D, uint32_t same) {
+    uint32_t m = 0;
+    for (uint32_t c = 0; c < D.n_cons; c++) m |= ((same >> D.lvl(c)) & 1u) << c;
+    return m;
+}
+
+// After phase_a of a leaf pass: parents whose base is a short list of a
+// constraint outside `shared` (flen elements) test it against a filter of the
+// shortest shared list; such a lane gets the filtered list's probe in slot
+// flt.vk.  The filter stays for later windows with the same list.
+//
+// A short list is tested in flattened tiles, where a search of the shared list
+// costs a chain of ~log2(length) loads of 64 addresses; the filter is one LDS
+// word.  Measured without and with it: three patterns on 30,011 nodes of degree
+// ~20 7.9 and 6.5 ms.  Long lists are streamed against dense rows or searched as
+// before: filtering them too, up to 2 / 4 / 8 times longer lists for the sake of
+// it, took 357 / 411 / 413 ms on 96 plans of R-MAT 22 instead of 347.
+__device__ __forceinline__ void use_filter(Ctx& C, const LK& D, uint32_t nb, uint32_t shared, uint32_t flen,
+                                           uint32_t& len, Filter& flt) {
+    const KArgs& a = *C.a;
+    const DevGraph& g = a.g;
+    const uint32_t lane = C.lane;
+    const bool el = len > 0 && flen < kWideMin && flen <= len;
+    const uint64_t em = __ballot(el);
+    if (!em) return;
+    uint32_t best = kSkip, bc = 0, bo = 0;
+    for (uint32_t c = 0; c < D.n_cons; c++) {
+        if (!((shared >> c) & 1u)) continue;
+        const uint32_t nd = uni(C.s.bound[D.lvl(c) * 64]);
+        const uint32_t* off = off_of(g, D.dir(c));
+        const uint32_t o = uni(off[nd]), l = uni(off[nd + 1]) - o;
+        if (l < best) {
+            best = l;
+            bc = c;
+            bo = o;
+        }
+    }
+    if (best == 0) return;
+    const uint32_t total = uni(__shfl(scan_incl(el ? flen : 0u, lane), 63, 64));
+    const uint64_t tag = reinterpret_cast<uint64_t>(adj_of(g, D.dir(bc)) + bo);
+    const uint64_t old = ((uint64_t)uni(C.s.st[28]) << 32) | uni(C.s.st[27]);
+    if (old != tag && total < 2u * best + 64u) return;  // not worth filling it
+    const uint32_t bits = 32u * a.filt_words;
+    flt.lanes = em;
+    flt.bits = C.s.filt;
+    flt.lim = g.n <= bits ? 0xFFFFFFFFu : bits / 2;
+    flt.vk = D.n_cons - 2;
+    if (old != tag) {
+        // clear the old list's bits one by one if that is less than the map
+        const uint32_t oldn = uni(C.s.st[29]);
+        if (old && oldn <= 2 * a.filt_words) {
+            const gptr L = (gptr)old;
+            for (uint32_t i = lane; i < oldn; i += 64) {
+                const uint32_t x = L[i];
+                C.s.filt[(x < flt.lim ? x : (flt.lim | (x & (flt.lim - 1u)))) >> 5] = 0;
+            }
+        } else {
+            uint4* z = reinterpret_cast<uint4*>(C.s.filt);
+            for (uint32_t i = lane; i < a.filt_words / 4; i += 64) z[i] = make_uint4(0, 0, 0, 0);
+        }
+        if (lane == 0) {
+            C.s.st[27] = (uint32_t)tag;
+            C.s.st[28] = (uint32_t)(tag >> 32);
+            C.s.st[29] = best;
+        }
+        wave_sync();
+        const gptr L = (gptr)tag;
+        for (uint32_t i = lane; i < best; i += 64) {
+            const uint32_t x = L[i];
+            const uint32_t h = x < flt.lim ? x : (flt.lim | (x & (flt.lim - 1u)));
+            atomicOr(&C.s.filt[h >> 5], 1u << (h & 31u));
+        }
+    }
+    if (el) {
+        uint32_t fb = kSkip, fc = 0, fo = 0;
+        for (uint32_t c = 0; c < D.n_cons; c++) {
+            if ((shared >> c) & 1u) continue;
+            const uint32_t nd = C.s.bound[D.lvl(c) * 64 + lane];
+            const uint32_t* off = off_of(g, D.dir(c));
+            const uint32_t o = off[nd], l = off[nd + 1] - o;
+            if (l < fb) {
+                fb = l;
+                fc = c;
+                fo = o;
+            }
+        }
+        uint32_t k = 0;
+        for (uint32_t c = 0; c < D.n_cons; c++) {
+            if (c == fc) continue;
+            const uint32_t nd = C.s.bound[D.lvl(c) * 64 + lane];
+            const uint32_t* off = off_of(g, D.dir(c));
+            const uint32_t o = off[nd];
+            uint32_t l = off[nd + 1] - o;
+            const uint64_t v = reinterpret_cast<uint64_t>(probe_ref(g, D.dir(c), nd, o, l));
+            const uint32_t s = c == bc ? flt.vk : k++;
+            C.s.slot_len[s * 64 + lane] = l;
+            C.s.slot_lo[s * 64 + lane] = (uint32_t)v;
+            C.s.slot_hi[s * 64 + lane] = (uint32_t)(v >> 32);
+        }
+        for (uint32_t s = D.n_cons - 1; s < n_slots(D); s++) C.s.slot_len[s * 64 + lane] = kSkip;
+        const uint32_t* base = adj_of(g, D.dir(fc)) + fo;
+        len = fb;
+        if (D.gt) sym_trim(C.s, D.gt, D.lt, nb, lane, base, len);
+        const uint64_t bv = reinterpret_cast<uint64_t>(base);
+        C.s.base_lo[lane] = (uint32_t)bv;
+        C.s.base_hi[lane] = (uint32_t)(bv >> 32);
+        C.s.base_len[lane] = len;
+    }
+    wave_sync();
+}
+
 // Expand one window of level lv from the parents in level lv-1.  Returns the
 // number of children written to level lv's buffer.
 __device__ __forceinline__ uint32_t expand(Ctx& C, uint32_t lv) {
@@ -929,8 +1109,8 @@ __device__ __forceinline__ uint32_t expand(Ctx& C, uint32_t lv) {
     const uint32_t pofs = uni(st[8 + lv]);
     const uint32_t p = cur + lane;
     const bool pv = p < nparents;
-    uint32_t brow, bskip;
-    uint32_t len = phase_a<false>(C, D, lv, p, pv, true, brow, bskip);
+    uint32_t flen, brow, bskip;
+    uint32_t len = phase_a<false>(C, D, lv, p, pv, true, ~0u, flen, brow, bskip);
     bool cut = false;
     if (uni(st[24]) == lv && uni(st[26]) != kSkip && pv) {
         // a donated id range: its part of the sorted base list
@@ -1007,7 +1187,7 @@ __device__ __forceinline__ uint32_t expand(Ctx& C, uint32_t lv) {
             okb = okb && lb < C.s.base_len[jb];
             if (oka) xa = base_elem(C, ja, la);
             if (okb) xb = base_elem(C, jb, lb);
-            check_pair(C, D, D.inj, lv, ns, ja, xa, oka, jb, xb, okb);
+            check_pair<false>(C, D, Filter{}, D.inj, lv, ns, ja, xa, oka, jb, xb, okb);
             const uint64_t ma = __ballot(oka);
             if (oka) {
                 const uint32_t pos = nout + rank_below(ma);
@@ -1117,112 +1297,6 @@ __device__ __forceinline__ uint32_t own_count(uint64_t ballot, uint32_t start, u
     const uint32_t a = lo - base, b = hi - base;
     const uint64_t m = (b == 64 ? ~0ull : ((1ull << b) - 1ull)) & ~((1ull << a) - 1ull);
     return (uint32_t)__popcll(ballot & m);
-}
-
-// Leaf group with several signatures: for every signature mask M the terms
-// use, h[M] = |intersection over s in M of S_s| is measured per partial match
-// (one flattened pass over the shortest list of M's constraints, or list
-// length minus bound hits when M has a single constraint list), then the
-// inclusion-exclusion terms over set partitions of the leaves are summed in
-// 128-bit integers.  The 64 lanes hold the 64 partial matches [w0, w0 + 64).
-__device__ __forceinline__ void leaf_masks(Ctx& C, uint32_t nb, uint32_t p, bool pv) {
-    const KArgs& a = *C.a;
-    const PlanDesc* P = C.P;
-    const uint32_t lane = C.lane;
-    const uint32_t n_masks = uni(P->n_masks);
-    for (uint32_t mi = 0; mi < n_masks; mi++) {
-        const LK K = load_lk(P->mdesc[mi], a);
-        uint32_t h = 0;
-        if (K.n_cons == 1 && K.reuse == kNoReuse) {
-            // one list L: |L| minus the bound nodes found in L
-            if (pv) {
-                const DevGraph& g = a.g;
-                const uint32_t nd = C.s.bound[K.lvl(0) * 64 + lane];
-                const uint32_t* off = off_of(g, K.dir(0));
-                const uint32_t o = off[nd], l = off[nd + 1] - o;
-                const uint32_t* L = adj_of(g, K.dir(0)) + o;
-                h = l;
-                for (uint32_t b = 0; b < nb; b++)
-                    if (((K.inj >> b) & 1u) && contains(L, l, C.s.bound[b * 64 + lane])) h -= 1;
-            }
-        } else {
-            uint32_t brow, bskip;
-            uint32_t len = phase_a<true>(C, K, nb, p, pv, false, brow, bskip);
-            const uint32_t ns = n_slots(K);
-            // long base lists are scanned one by one after the flattened pass
-            Par P1 = parent_view(C, ns, len);
-            const bool wd = len >= kWideMin && !K.deg_check;
-            const bool rows = wd && P1.rows_only && P1.n_rows > 0 && P1.len > 0;
-            uint64_t wide = __ballot(wd && P1.len > 0 && !rows);
-            Dense dn{};
-            if (rows) dn = take_dense(C, K, nb, brow, bskip, P1);
-            const uint64_t words = __ballot(dn.w1 > dn.w0), chunks = __ballot(rows && P1.len > 0);
-            if (wd) len = 0;
-            const uint32_t incl = scan_incl(len, lane);
-            C.s.incl[lane] = incl;
-            const uint32_t T = uni(__shfl(incl, 63, 64));
-            const bool owns = len > 0;
-            const uint32_t start = incl - len;
-            wave_sync();
-            uint32_t carry = 0;
-            for (uint32_t t0 = 0; t0 < T; t0 += 128) {
-                const uint32_t ga = t0 + lane, gb = t0 + 64 + lane;
-                uint32_t ja, jb;
-                tile_parents(C.s, lane, t0, start, owns, carry, ja, jb);
-                const uint32_t la = ga - (ja ? C.s.incl[ja - 1] : 0u);
-                const uint32_t lb = gb - (jb ? C.s.incl[jb - 1] : 0u);
-                bool oka = ga < T && la < C.s.base_len[ja];
-                bool okb = gb < T && lb < C.s.base_len[jb];
-                uint32_t xa = 0, xb = 0;
-                if (oka) xa = base_elem(C, ja, la);
-                if (okb) xb = base_elem(C, jb, lb);
-                // injectivity is settled per partial match below
-                check_pair(C, K, 0u, nb, ns, ja, xa, oka, jb, xb, okb);
-                const uint64_t ba = __ballot(oka), bb = __ballot(okb);
-                if (owns) h += own_count(ba, start, len, t0) + own_count(bb, start, len, t0 + 64);
-            }
-            if (words)
-                word_scan(C, P1, dn, K.gt != 0, words, [&](uint32_t j, uint32_t v) {
-                    const uint32_t n = uni(__shfl(scan_incl(v, lane), 63, 64));
-                    h += lane == j ? n : 0u;
-                });
-            if (chunks) chunk_scan(C, P1, chunks, [&](uint32_t j, uint32_t n) { h += lane == j ? n : 0u; });
-            for (; wide; wide &= wide - 1) {
-                const uint32_t j = (uint32_t)__builtin_ctzll(wide);
-                const uint32_t cnt = wide_count(C, K, nb, ns, j);
-                h = lane == j ? cnt : h;
-            }
-            // the bound nodes the set may not contain were counted if present
-            if (pv)
-                for (uint32_t b = 0; b < nb; b++)
-                    if (((K.inj >> b) & 1u) && bound_in_set(C, ns, C.s.bound[b * 64 + lane])) h -= 1;
-            wave_sync();
-        }
-        // every mask whose test is this entry's takes its size
-        for (uint32_t ms = uni(P->mask_set[mi]) & 0xFFFEu; ms; ms &= ms - 1)
-            C.s.hist[lane * 16 + (uint32_t)__builtin_ctz(ms)] = h;
-    }
-    wave_sync();
-    if (pv) {
-        // inclusion-exclusion over set partitions of the leaves; a term whose
-        // magnitude could pass 2^120 marks the plan as overflowed
-        const uint32_t* h = C.s.hist + lane * 16;
-        __int128 val = 0;
-        bool big = false;
-        const uint32_t n_terms = uni(P->n_terms);
-        for (uint32_t t = 0; t < n_terms; t++) {
-            const Term& tm = P->terms[t];
-            uint32_t hv[kMaxBlocks];
-            const uint32_t nb = tm.nb < kMaxBlocks ? tm.nb : kMaxBlocks;
-            for (uint32_t b = 0; b < nb; b++) hv[b] = h[tm.mask[b] & 15u];
-            val += ie_term(tm.coef, hv, nb, &big);
-        }
-        // the injective count of one partial match is never negative
-        const unsigned __int128 v = (unsigned __int128)(val < 0 ? (__int128)0 : val);
-        if (big || val < 0) C.ovf = true;
-        if (u128_add(C.acc_lo, C.acc_hi, (unsigned long long)v, (unsigned long long)(v >> 64))) C.ovf = true;
-    }
-    wave_sync();
 }
 
 // Listing: the survivors of a tile pair are whole embeddings (bound levels
@@ -1386,14 +1460,192 @@ __device__ __forceinline__ uint32_t donate_leaves(Ctx& C, uint32_t lv, uint32_t 
     return uni(__shfl(b, (int)__builtin_ctzll(m), 64));
 }
 
+// Size of descriptor D's candidate set (a leaf signature or a signature mask)
+// for each partial match of the window, the bound nodes it may not hold taken
+// off.  SUM: the sizes' sum (the same for every lane) instead, for plans with
+// one leaf; only then a launch may be listing or merging.
+template <bool SUM, bool ROOMY>
+__device__ __forceinline__ unsigned long long leaf_set(Ctx& C, const LK& D, uint32_t nb, uint32_t p, bool pv,
+                                                       uint32_t same) {
+    const KArgs& a = *C.a;
+    const uint32_t lane = C.lane;
+    const bool listing = SUM && a.list != nullptr;
+    const uint32_t shared = shared_cons(D, same);
+    uint32_t flen, brow, bskip;
+    uint32_t len = phase_a<true>(C, D, nb, p, pv, false, shared, flen, brow, bskip);
+    const uint32_t ns = n_slots(D);
+    Filter flt{};
+    flt.vk = kSkip;
+    if (ROOMY && shared) use_filter(C, D, nb, shared, flen, len, flt);
+    // one leaf whose set is a base list and one probe list: balanced big pairs
+    // leave the flattened pass for the cooperative merge
+    bool big = false;
+    if (SUM && a.merge_min != 0xFFFFFFFFu && pv && !listing) {
+        uint32_t nprobe = 0, pl = 0;
+        for (uint32_t c = 0; c < ns; c++)
+            if (C.s.slot_len[c * 64 + lane] != kSkip) {
+                pl = C.s.slot_len[c * 64 + lane];
+                nprobe++;
+            }
+        if (nprobe == 1 && pl != kRowLen) {
+            const uint32_t mn = len < pl ? len : pl, mx = len < pl ? pl : len;
+            big = mn >= a.merge_min && (uint64_t)mx <= (uint64_t)a.merge_ratio * mn;
+        }
+    }
+    uint64_t bigmask = SUM ? __ballot(big) : 0ull;
+    // long base lists leave the flattened pass too (listing stays flattened)
+    Par P1 = parent_view(C, ns, len);
+    const bool wd = len >= kWideMin && !big && !listing && !D.deg_check;
+    const bool rows = wd && P1.rows_only && P1.n_rows > 0 && P1.len > 0;
+    uint64_t wide = __ballot(wd && P1.len > 0 && !rows);
+    Dense dn{};
+    if (rows) dn = take_dense(C, D, nb, brow, bskip, P1);
+    const uint64_t words = __ballot(dn.w1 > dn.w0), chunks = __ballot(rows && P1.len > 0);
+    if (big || wd) len = 0;
+    const uint32_t incl = scan_incl(len, lane);
+    C.s.incl[lane] = incl;
+    const uint32_t T = uni(__shfl(incl, 63, 64));
+    const bool owns = len > 0;
+    const uint32_t start = incl - len;
+    wave_sync();
+    unsigned long long lin = 0;
+    uint32_t h = 0, carry = 0;
+    // two tiles per step
+    for (uint32_t t0 = 0; t0 < T; t0 += 128) {
+        const uint32_t ga = t0 + lane, gb = t0 + 64 + lane;
+        uint32_t ja, jb;
+        tile_parents(C.s, lane, t0, start, owns, carry, ja, jb);
+        const uint32_t la = ga - (ja ? C.s.incl[ja - 1] : 0u);
+        const uint32_t lb = gb - (jb ? C.s.incl[jb - 1] : 0u);
+        bool oka = ga < T && la < C.s.base_len[ja];
+        bool okb = gb < T && lb < C.s.base_len[jb];
+        uint32_t xa = 0, xb = 0;
+        if (oka) xa = base_elem(C, ja, la);
+        if (okb) xb = base_elem(C, jb, lb);
+        // injectivity is settled per partial match below (per element when
+        // every embedding is written out)
+        check_pair<ROOMY>(C, D, flt, listing ? D.inj : 0u, nb, ns, ja, xa, oka, jb, xb, okb);
+        const uint64_t ma = __ballot(oka), mb = __ballot(okb);
+        if (SUM) {
+            lin += (unsigned long long)(__popcll(ma) + __popcll(mb));
+            if (listing) write_rows(C, nb, ma, mb, ja, xa, oka, jb, xb, okb);
+        } else if (owns) {
+            h += own_count(ma, start, len, t0) + own_count(mb, start, len, t0 + 64);
+        }
+    }
+    auto add = [&](uint32_t j, uint32_t n) {
+        if (SUM) lin += n;
+        else h += lane == j ? n : 0u;
+    };
+    if (words) {
+        uint32_t vacc = 0;  // SUM: this lane's share of all chunks
+        word_scan(C, P1, dn, D.gt != 0, words, [&](uint32_t j, uint32_t v) {
+            if (SUM) vacc += v;
+            else add(j, uni(__shfl(scan_incl(v, lane), 63, 64)));
+        });
+        // (64 lists of the largest size stay below 2^32 elements)
+        if (SUM) lin += uni(__shfl(scan_incl(vacc, lane), 63, 64));
+    }
+    if (chunks) chunk_scan<ROOMY>(C, P1, chunks, add);
+    for (; wide; wide &= wide - 1) {
+        const uint32_t j = (uint32_t)__builtin_ctzll(wide);
+        add(j, wide_count(C, D, nb, ns, j));
+    }
+    // the bound nodes the set may not contain were counted if present
+    for (uint32_t b = 0; b < nb && !listing; b++) {
+        if (!((D.inj >> b) & 1u)) continue;
+        const bool hit = pv && !big && bound_in_set(C, ns, C.s.bound[b * 64 + lane]);
+        if (SUM) lin -= (unsigned long long)__popcll(__ballot(hit));
+        else h -= hit ? 1u : 0u;
+    }
+    wave_sync();
+    // balanced big pairs, one partial match at a time
+    for (; SUM && bigmask; bigmask &= bigmask - 1) {
+        const uint32_t j = (uint32_t)__builtin_ctzll(bigmask);
+        const uint32_t blen = uni(C.s.base_len[j]);
+        uint32_t pc = 0;
+        for (uint32_t c = 0; c < ns; c++)
+            if (C.s.slot_len[c * 64 + j] != kSkip) pc = c;
+        pc = uni(pc);
+        const uint32_t plen = uni(C.s.slot_len[pc * 64 + j]);
+        const gptr A = join_ptr(uni(C.s.base_lo[j]), uni(C.s.base_hi[j]));
+        const gptr B = join_ptr(uni(C.s.slot_lo[pc * 64 + j]), uni(C.s.slot_hi[pc * 64 + j]));
+        lin += merge_count(C.s, A, blen, B, plen, D.inj, nb, j, lane);
+    }
+    return SUM ? lin : (unsigned long long)h;
+}
+
+// The same for a descriptor with one list L and no reuse: |L| (the part beyond
+// the symmetry bound) minus the bound nodes found in it, per partial match.
+__device__ __forceinline__ uint32_t leaf_list(const Ctx& C, const LK& D, uint32_t nb, bool pv) {
+    if (!pv) return 0;
+    const uint32_t lane = C.lane;
+    const DevGraph& g = C.a->g;
+    const uint32_t nd = C.s.bound[D.lvl(0) * 64 + lane];
+    const uint32_t* off = off_of(g, D.dir(0));
+    const uint32_t o = off[nd];
+    uint32_t l = off[nd + 1] - o;
+    const uint32_t* L = adj_of(g, D.dir(0)) + o;
+    if (D.gt) sym_trim(C.s, D.gt, D.lt, nb, lane, L, l);
+    uint32_t v = l;
+    for (uint32_t b = 0; b < nb; b++)
+        if (((D.inj >> b) & 1u) && contains(L, l, C.s.bound[b * 64 + lane])) v -= 1;
+    return v;
+}
+
+// Leaf group of the 64 partial matches of a window, lane by lane: the plan's
+// one signature (linear), or several: for every signature mask M the terms
+// use, h[M] = |intersection over s in M of S_s| is measured, then the
+// inclusion-exclusion terms over set partitions of the leaves are summed in
+// 128-bit integers.
+template <bool ROOMY>
+__device__ __forceinline__ void leaf_masks(Ctx& C, uint32_t nb, uint32_t p, bool pv, uint32_t same) {
+    const KArgs& a = *C.a;
+    const PlanDesc* P = C.P;
+    const uint32_t lane = C.lane;
+    const bool linear = uni(P->linear) != 0;
+    const uint32_t n_masks = linear ? 1u : uni(P->n_masks);
+    for (uint32_t mi = 0; mi < n_masks; mi++) {
+        const LK K = load_lk(linear ? P->sig[0] : P->mdesc[mi], a);
+        const uint32_t h = K.n_cons == 1 && K.reuse == kNoReuse
+                               ? leaf_list(C, K, nb, pv)
+                               : (uint32_t)leaf_set<false, ROOMY>(C, K, nb, p, pv, same);
+        if (linear) {
+            if (u128_add(C.acc_lo, C.acc_hi, h, 0ull)) C.ovf = true;
+            return;
+        }
+        // every mask whose test is this entry's takes its size
+        for (uint32_t ms = uni(P->mask_set[mi]) & 0xFFFEu; ms; ms &= ms - 1)
+            C.s.hist[(uint32_t)__builtin_ctz(ms) * 64 + lane] = h;
+    }
+    wave_sync();
+    if (pv) {
+        // inclusion-exclusion over set partitions of the leaves; a term whose
+        // magnitude could pass 2^120 marks the plan as overflowed
+        __int128 val = 0;
+        bool big = false;
+        const uint32_t n_terms = uni(P->n_terms);
+        for (uint32_t t = 0; t < n_terms; t++) {
+            const Term& tm = P->terms[t];
+            uint32_t hv[kMaxBlocks];
+            const uint32_t nb = tm.nb < kMaxBlocks ? tm.nb : kMaxBlocks;
+            for (uint32_t b = 0; b < nb; b++) hv[b] = C.s.hist[(tm.mask[b] & 15u) * 64 + lane];
+            val += ie_term(tm.coef, hv, nb, &big);
+        }
+        // the injective count of one partial match is never negative
+        const unsigned __int128 v = (unsigned __int128)(val < 0 ? (__int128)0 : val);
+        if (big || val < 0) C.ovf = true;
+        if (u128_add(C.acc_lo, C.acc_hi, (unsigned long long)v, (unsigned long long)(v >> 64))) C.ovf = true;
+    }
+    wave_sync();
+}
+
 // Count the leaf group for every partial match in level `lv` (= e - 1).
-template <bool NONLIN>
+template <bool NONLIN, bool ROOMY>
 __device__ __forceinline__ void count_leaves(Ctx& C, uint32_t lv, uint32_t nprefix) {
     const KArgs& a = *C.a;
     const PlanDesc* P = C.P;
     const uint32_t lane = C.lane;
-    const uint32_t nsig = uni(P->n_sig);
-    const bool linear = !NONLIN || P->linear != 0;
     const uint32_t nb = lv + 1;  // bound levels 0..lv
     const LK S0 = load_lk(P->sig[0], a);
     const uint32_t entered = (uint32_t)__builtin_readcyclecounter();
@@ -1423,122 +1675,19 @@ __device__ __forceinline__ void count_leaves(Ctx& C, uint32_t lv, uint32_t npref
                 if (l > 0) idx = F.parent[idx];
             }
         }
-        unsigned long long lin = 0;
-        if (!linear) {
-            leaf_masks(C, nb, p, pv);
-            continue;
-        }
-        const bool listing = a.list != nullptr;
-        if (!listing && S0.n_cons == 1 && S0.reuse == kNoReuse) {
-            // one leaf drawn from one list L: |L| minus the bound nodes found in L
-            uint32_t v = 0;
-            if (pv) {
-                const DevGraph& g = a.g;
-                uint32_t nd = C.s.bound[S0.lvl(0) * 64 + lane];
-                const uint32_t* off = off_of(g, S0.dir(0));
-                uint32_t o = off[nd];
-                uint32_t l = off[nd + 1] - o;
-                const uint32_t* L = adj_of(g, S0.dir(0)) + o;
-                if (S0.gt) sym_trim(C.s, S0.gt, S0.lt, nb, lane, L, l);
-                v = l;
-                for (uint32_t b = 0; b < nb; b++)
-                    if (((S0.inj >> b) & 1u) && contains(L, l, C.s.bound[b * 64 + lane])) v -= 1;
+        const uint32_t same = ROOMY && a.filt_words ? same_levels(C, nb, pv) : 0u;
+        if (NONLIN) {
+            leaf_masks<ROOMY>(C, nb, p, pv, same);
+        } else {
+            unsigned long long v = 0;
+            if (a.list == nullptr && S0.n_cons == 1 && S0.reuse == kNoReuse) {
+                v = leaf_list(C, S0, nb, pv);
+            } else {
+                v = leaf_set<true, ROOMY>(C, S0, nb, p, pv, same);
+                v = lane == 0 ? v : 0ull;
             }
             if (u128_add(C.acc_lo, C.acc_hi, v, 0ull)) C.ovf = true;
-            wave_sync();
-            continue;
         }
-        {
-            // one leaf signature
-            const LK& S = S0;
-            uint32_t brow, bskip;
-            uint32_t len = phase_a<true>(C, S, nb, p, pv, false, brow, bskip);
-            // one leaf whose set is a base list and one probe list: balanced big
-            // pairs leave the flattened pass for the cooperative merge
-            uint32_t probe_c = kSkip;
-            bool big = false;
-            const uint32_t ns = n_slots(S);
-            if (linear && pv && !listing) {
-                uint32_t nprobe = 0;
-                for (uint32_t c = 0; c < ns; c++)
-                    if (C.s.slot_len[c * 64 + lane] != kSkip) {
-                        probe_c = c;
-                        nprobe++;
-                    }
-                if (nprobe == 1 && C.s.slot_len[probe_c * 64 + lane] != kRowLen) {
-                    uint32_t pl = C.s.slot_len[probe_c * 64 + lane];
-                    uint32_t mn = len < pl ? len : pl, mx = len < pl ? pl : len;
-                    big = mn >= a.merge_min && (uint64_t)mx <= (uint64_t)a.merge_ratio * mn;
-                }
-            }
-            uint64_t bigmask = __ballot(big);
-            // other long base lists are scanned one by one (listing stays flattened)
-            Par P1 = parent_view(C, ns, len);
-            const bool wd = len >= kWideMin && !big && !listing && !S.deg_check;
-            const bool rows = wd && P1.rows_only && P1.n_rows > 0 && P1.len > 0;
-            uint64_t wide = __ballot(wd && P1.len > 0 && !rows);
-            Dense dn{};
-            if (rows) dn = take_dense(C, S, nb, brow, bskip, P1);
-            const uint64_t words = __ballot(dn.w1 > dn.w0), chunks = __ballot(rows && P1.len > 0);
-            if (big || wd) len = 0;
-            (void)nsig;
-            const uint32_t incl = scan_incl(len, lane);
-            C.s.incl[lane] = incl;
-            const uint32_t T = uni(__shfl(incl, 63, 64));
-            const bool owns = len > 0;
-            const uint32_t start = incl - len;
-            wave_sync();
-            uint32_t carry = 0;
-            // two tiles per step
-            for (uint32_t t0 = 0; t0 < T; t0 += 128) {
-                const uint32_t ga = t0 + lane, gb = t0 + 64 + lane;
-                uint32_t ja, jb;
-                tile_parents(C.s, lane, t0, start, owns, carry, ja, jb);
-                const uint32_t la = ga - (ja ? C.s.incl[ja - 1] : 0u);
-                const uint32_t lb = gb - (jb ? C.s.incl[jb - 1] : 0u);
-                bool oka = ga < T && la < C.s.base_len[ja];
-                bool okb = gb < T && lb < C.s.base_len[jb];
-                uint32_t xa = 0, xb = 0;
-                if (oka) xa = base_elem(C, ja, la);
-                if (okb) xb = base_elem(C, jb, lb);
-                // injectivity is settled per partial match below (per element
-                // when every embedding is written out)
-                check_pair(C, S, listing ? S.inj : 0u, nb, ns, ja, xa, oka, jb, xb, okb);
-                // one leaf: survivors are only counted
-                const uint64_t ma = __ballot(oka), mb = __ballot(okb);
-                lin += (unsigned long long)(__popcll(ma) + __popcll(mb));
-                if (listing) write_rows(C, nb, ma, mb, ja, xa, oka, jb, xb, okb);
-            }
-            uint32_t vacc = 0;  // this lane's share of the word scans
-            if (words) word_scan(C, P1, dn, S.gt != 0, words, [&](uint32_t, uint32_t v) { vacc += v; });
-            // (64 lists of the largest size stay below 2^32 elements)
-            if (words) lin += uni(__shfl(scan_incl(vacc, lane), 63, 64));
-            if (chunks) chunk_scan(C, P1, chunks, [&](uint32_t, uint32_t n) { lin += n; });
-            for (; wide; wide &= wide - 1)
-                lin += wide_count(C, S, nb, ns, (uint32_t)__builtin_ctzll(wide));
-            // bound nodes the leaf may not take were counted if they are in the set
-            for (uint32_t b = 0; b < nb && !listing; b++) {
-                if (!((S.inj >> b) & 1u)) continue;
-                const bool hit = pv && !big && bound_in_set(C, ns, C.s.bound[b * 64 + lane]);
-                lin -= (unsigned long long)__popcll(__ballot(hit));
-            }
-            wave_sync();
-            // balanced big pairs, one partial match at a time
-            while (bigmask) {
-                const uint32_t j = (uint32_t)__builtin_ctzll(bigmask);
-                bigmask &= bigmask - 1;
-                const uint32_t blen = uni(C.s.base_len[j]);
-                uint32_t pc = 0;
-                for (uint32_t c = 0; c < ns; c++)
-                    if (C.s.slot_len[c * 64 + j] != kSkip) pc = c;
-                pc = uni(pc);
-                const uint32_t plen = uni(C.s.slot_len[pc * 64 + j]);
-                const gptr A = join_ptr(uni(C.s.base_lo[j]), uni(C.s.base_hi[j]));
-                const gptr B = join_ptr(uni(C.s.slot_lo[pc * 64 + j]), uni(C.s.slot_hi[pc * 64 + j]));
-                lin += merge_count(C.s, A, blen, B, plen, S.inj, nb, j, lane);
-            }
-        }
-        if (lane == 0 && u128_add(C.acc_lo, C.acc_hi, lin, 0ull)) C.ovf = true;
         wave_sync();
     }
 }
@@ -1564,12 +1713,12 @@ __device__ __forceinline__ void flush(Ctx& C) {
 
 // Depth-first exploration of the n0 partial matches held in level start-1
 // (start = 1: roots in level 0).
-template <bool NONLIN>
+template <bool NONLIN, bool ROOMY>
 __device__ __forceinline__ void explore(Ctx& C, uint32_t n0, uint32_t start) {
     const uint32_t e = C.P->e;
     uint32_t* st = C.s.st;
     if (e == 1) {
-        count_leaves<NONLIN>(C, 0, n0);
+        count_leaves<NONLIN, ROOMY>(C, 0, n0);
         return;
     }
     if (C.lane == 0) {
@@ -1602,7 +1751,7 @@ __device__ __forceinline__ void explore(Ctx& C, uint32_t n0, uint32_t start) {
         if (lv >= 2 && time_to_look(C) && C.looked - C.begun >= kDonateParents) donate_parents(C, start, lv);
         uint32_t nout = expand(C, lv);
         if (lv == e - 1) {
-            if (nout) count_leaves<NONLIN>(C, lv, nout);
+            if (nout) count_leaves<NONLIN, ROOMY>(C, lv, nout);
             if (C.stop) break;
         } else if (nout) {
             lv += 1;
@@ -1621,6 +1770,7 @@ __device__ __forceinline__ void explore(Ctx& C, uint32_t n0, uint32_t start) {
 // the whole kernel in registers) for launches of at most that many.
 template <bool NONLIN, int MINB>
 __global__ void __launch_bounds__(kBlockThreads, MINB) count_kernel(KArgs a) {
+    constexpr bool ROOMY = MINB <= kRoomyBlocksPerCu;
     extern __shared__ uint32_t smem[];
     Ctx C;
     C.a = &a;
@@ -1628,7 +1778,8 @@ __global__ void __launch_bounds__(kBlockThreads, MINB) count_kernel(KArgs a) {
     // uniform over the wave, stated so: what is addressed from it stays in scalar
     // registers (roomy kernels 168 -> 142 and 161 -> 133 VGPRs)
     const uint32_t wid = uni(threadIdx.x >> 6);
-    C.s = carve(smem + wid * a.lds_words, a.lds_rows, a.maxc, a.merge_min != 0xFFFFFFFFu);
+    C.s = carve(smem + wid * a.lds_words, a.lds_rows, a.maxc, a.merge_min != 0xFFFFFFFFu,
+                a.filt_words);
     const uint64_t gw = (uint64_t)blockIdx.x * kWavesPerBlock + wid;
     C.scr = a.scratch + gw * (uint64_t)a.wave_words;
     C.acc_lo = C.acc_hi = 0;
@@ -1646,6 +1797,7 @@ __global__ void __launch_bounds__(kBlockThreads, MINB) count_kernel(KArgs a) {
     // 64-bit: the host keeps the product below 2^32 (root items are 32-bit)
     const uint64_t chunks_per_plan = ((uint64_t)a.n_src + a.chunk - 1) / a.chunk;
     const uint64_t total_chunks = chunks_per_plan * a.n_plans;
+    if (C.lane < 3) C.s.st[27 + C.lane] = 0;  // no list is in the filter yet
     Lvl F0 = lvl_arrays(C.scr, a.cap, 0);
     uint32_t taken = 0;
     // root items (item = chunk index x n_plans + plan) come from kQueues
@@ -1906,7 +2058,7 @@ __global__ void __launch_bounds__(kBlockThreads, MINB) count_kernel(KArgs a) {
         }
         if (C.lane == 0) C.s.st[24] = kind == 3 ? start : 0u;
         wave_sync();
-        if (n0) explore<NONLIN>(C, n0, start);
+        if (n0) explore<NONLIN, ROOMY>(C, n0, start);
         if (C.stop) break;
     }
     // a wave that was counted as active must not stay so after a cancel

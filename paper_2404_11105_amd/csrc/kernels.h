@@ -86,6 +86,8 @@ struct DevGraph {
     uint32_t pad;
 };
 
+constexpr uint32_t kLdsPerCu = 160u << 10;  // gfx950
+constexpr uint32_t kFilterMinWords = 256, kFilterMaxWords = 2048;  // a wave's shared-list filter
 constexpr uint32_t kNoRows = 0xFFFFFFFFu;
 constexpr uint32_t kRowLen = 0xFFFFFFFEu;  // probe-list length marker: test a dense row
 
@@ -121,6 +123,7 @@ struct KArgs {
     uint32_t lds_words;         // LDS words per wave
     uint32_t lds_rows;          // bound / ancestor rows (largest enumerated depth)
     uint32_t maxc;              // largest constraint count over plans and signatures
+    uint32_t filt_words;        // LDS words of a wave's shared-list bit map (a power of two; 0: none)
     uint32_t nonlinear;         // some plan counts a leaf group of several vertices
     uint32_t n_cu;              // compute units of the device (picks the register budget)
     uint32_t merge_min;         // cooperative merge thresholds
@@ -208,13 +211,13 @@ __host__ __device__ inline bool in_root_share(uint32_t r, uint32_t s) {
 
 // LDS words per wave: `rows` bound levels (the largest enumerated depth of
 // the batch), the largest constraint count, and the optional parts.
-inline uint32_t lds_words_for(uint32_t rows, uint32_t maxc, bool nonlinear, bool merge) {
+inline uint32_t lds_words_for(uint32_t rows, uint32_t maxc, uint32_t masks, bool merge) {
     return 2 * rows * 64       // bound values, ancestor indices
            + 7 * 64            // base address (2 words) and length, inclusive scan, segment
                                // counts, tile parent marks (2 x 64)
            + 3 * maxc * 64     // probe slots: length, address (two words) per constraint
            + (merge ? kMergeChunk : 0)  // merge chunk
-           + (nonlinear ? 16 * 64 : 0)  // leaf-group histograms
+           + masks * 64        // set sizes per signature mask (0: no plan needs them)
            + 32;               // wave state
 }
 

@@ -100,7 +100,7 @@ int plan_device_desc(xm_plan_t* p, int dev, const PlanDesc** out) {
 }
 
 struct Layout {
-    uint32_t chunk, split, split_work, cap, waves_per_cu, n_waves, n_blocks, launch_blocks, e_max, maxc, merge_min, don_cap;
+    uint32_t chunk, split, split_work, cap, waves_per_cu, n_waves, n_blocks, launch_blocks, e_max, maxc, merge_min, don_cap, filt_words;
     bool nonlinear;
     size_t off_ctl, off_flags, off_partial, off_table, off_split, off_don, off_scratch, total;
     uint32_t split_cap, wave_words, lds_words;
@@ -157,6 +157,7 @@ int make_layout(const xm_graph_t* g, uint32_t n_plans, const xm_plan_t* const* p
     L.e_max = 1;
     L.maxc = 1;
     L.nonlinear = false;
+    uint32_t masks = 0;  // signature masks of the plan with the most (a power of two)
     uint32_t splittable = 0;
     for (uint32_t i = 0; i < n_plans; i++) {
         if (!plans[i]) return fail(XM_ERR_INVALID, "plan is NULL");
@@ -166,7 +167,10 @@ int make_layout(const xm_graph_t* g, uint32_t n_plans, const xm_plan_t* const* p
         for (uint32_t s = 0; s < D.n_sig; s++) L.maxc = std::max<uint32_t>(L.maxc, D.sig[s].n_cons);
         // a signature mask unites the constraints of several signatures
         for (uint32_t i = 0; i < D.n_masks; i++) L.maxc = std::max<uint32_t>(L.maxc, D.mdesc[i].n_cons);
-        if (!D.linear) L.nonlinear = true;
+        if (!D.linear) {
+            L.nonlinear = true;
+            masks = std::max(masks, 1u << D.n_sig);
+        }
         if (D.e >= 2) splittable++;
         // a symmetry-broken plan counts one embedding per orbit: neither the
         // embeddings of a root subset nor a listing can be read from it
@@ -181,17 +185,34 @@ int make_layout(const xm_graph_t* g, uint32_t n_plans, const xm_plan_t* const* p
             return fail(XM_ERR_INVALID, "listing needs a plan without XM_PLAN_SYMMETRY");
     }
     L.merge_min = (o && o->merge_min) ? o->merge_min : xm::kMergeMin;
-    L.lds_words = xm::lds_words_for(L.e_max, L.maxc, L.nonlinear, L.merge_min != 0xFFFFFFFFu);
+    const bool merging = L.merge_min != 0xFFFFFFFFu;
+    L.filt_words = 0;
+    L.lds_words = xm::lds_words_for(L.e_max, L.maxc, masks, merging);
     if (L.waves_per_cu == 0) {
         // as many waves as can be resident at once: the kernel is persistent.
         // When LDS leaves room for fewer than 6 blocks of the 64-VGPR kernel,
         // its extra occupancy does not pay for its spills: take the kernel
         // that keeps everything in registers at its kRoomyBlocksPerCu blocks
         // (measured: 256 plans on R-MAT 22 1,340 ms at 3 blocks against
-        // 1,374 ms at 4; TT4 + pendant on R-MAT 20 2,199 ms against 2,787 ms)
+        // 1,374 ms at 4; TT4 + pendant on R-MAT 20 2,199 ms against 2,787 ms).
+        // So too on a graph without long lists: there the filter of shared
+        // lists, which only that kernel has, saves more than the waves hide
+        // (four motifs on 2,000 nodes 288 us at 8 blocks, 256 us at 3).
         int bpc = xm::count_blocks_per_cu(L.nonlinear, (size_t)L.lds_words * 4 * xm::kWavesPerBlock);
-        if (bpc < 6) bpc = std::min(bpc, xm::kRoomyBlocksPerCu);
+        if (bpc < 6 || g->n_hubs == 0) bpc = std::min(bpc, xm::kRoomyBlocksPerCu);
         L.waves_per_cu = (uint32_t)std::max(1, std::min(bpc, 8)) * xm::kWavesPerBlock;
+    }
+    const uint32_t blocks = (L.waves_per_cu + xm::kWavesPerBlock - 1) / xm::kWavesPerBlock;
+    if (!merging && !(full_opts && o->list_dev) && blocks <= (uint32_t)xm::kRoomyBlocksPerCu) {
+        // the largest bit map that the resident blocks' LDS leaves room for, at
+        // most one bit a node
+        const size_t room =
+            std::min<size_t>(xm::kLdsPerCu / blocks - 1280, g->max_lds_block) / (4 * xm::kWavesPerBlock);
+        uint32_t want = xm::kFilterMinWords;
+        while (want < xm::kFilterMaxWords && (uint64_t)want * 32 < g->n) want *= 2;
+        for (uint32_t w = want; w >= xm::kFilterMinWords && !L.filt_words; w /= 2)
+            if (L.lds_words + w <= room) L.filt_words = w;
+        L.lds_words += L.filt_words;
     }
     L.n_waves = (uint32_t)g->n_cu * L.waves_per_cu;
     L.n_waves = (L.n_waves + xm::kWavesPerBlock - 1) / xm::kWavesPerBlock * xm::kWavesPerBlock;
@@ -388,6 +409,7 @@ int enqueue_count(const xm_graph_t* g, uint32_t n_plans, const xm_plan_t* const*
     a.lds_words = L.lds_words;
     a.lds_rows = L.e_max;
     a.maxc = L.maxc;
+    a.filt_words = L.filt_words;
     a.merge_min = L.merge_min;
     a.merge_ratio = (o && o->merge_ratio) ? o->merge_ratio : xm::kMergeRatio;
     a.nonlinear = L.nonlinear ? 1u : 0u;

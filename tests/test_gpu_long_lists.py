@@ -118,3 +118,29 @@ def test_one_heavy_root_is_shared_out(xa, reduced):
         for opts in (dict(split=4096, split_work=1 << 30), dict(split=4096, split_work=1 << 30, cap=4096, chunk=1)):
             print("[case]", name, reduced, opts, flush=True)
             assert xa.count(G, [plan], roots=hub, **opts) == [want]
+
+
+@pytest.mark.parametrize("n", [63, 8192, 8193, 65536, 65537, 150001])
+def test_short_lists_against_a_shared_list(xa, n):
+    """Short lists tested against a bit map of a list that a window shares: id
+    ranges at the map's sizes (every id its own bit, or ids that share bits),
+    kept and refilled between windows and plans, with one and with two leaves,
+    and with too little LDS for the whole map."""
+    rng = np.random.default_rng(n)
+    m = 6 * n
+    u, v = rng.integers(0, n, (2, m))
+    # some arcs between ids that share low bits, and triangles to find
+    w = (u[: m // 8] + 32768 * rng.integers(0, 4, m // 8)) % n
+    src = np.concatenate([u, v[: m // 8], u[: m // 8]])
+    dst = np.concatenate([v, w, w])
+    g = xmgen.from_arcs(n, src, dst)
+    P = xmgen.Pattern
+    pats = [xmgen.named("ffl"), xmgen.named("c3"), xmgen.named("c4"), xmgen.named("c5chord"),
+            P(4, ((0, 1), (0, 2), (1, 2), (0, 3), (1, 3)))]
+    want = [oracle.count(g, p) for p in pats]
+    G = xa.Graph(g)
+    for opts in (dict(), dict(waves_per_cu=4), dict(waves_per_cu=12), dict(waves_per_cu=16), dict(cap=64, split=64)):
+        print("[case]", n, opts, flush=True)
+        for reduced in (True, False):
+            assert xa.count(G, [xa.Plan(p, reduced=reduced, graph=G) for p in pats], **opts) == want
+        assert xa.count(G, [xa.Plan(p, graph=G, symmetry="above") for p in pats[:3]], **opts) == want[:3]
