@@ -2068,37 +2068,52 @@ __global__ void __launch_bounds__(kBlockThreads, MINB) count_kernel(KArgs a) {
 
 // Hub roots whose first-level list is longer than `split` become several
 // queued sub-range tasks.  Must agree with the root filter of count_kernel.
+// A lane looks at one (root, plan); the wave writes the tasks of its lanes one
+// after the other, 64 at a time (a root has up to kMaxPieces tasks: written by
+// its own lane they took 170 us).
 __global__ void split_kernel(KArgs a) {
     const uint32_t nsrc = a.roots ? a.n_src : a.n_hubs;
     const uint64_t total = (uint64_t)nsrc * a.n_plans;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total;
-         i += (uint64_t)gridDim.x * blockDim.x) {
+    const uint32_t lane = lane_id();
+    for (uint64_t i0 = (uint64_t)blockIdx.x * blockDim.x + (threadIdx.x & ~63u); i0 < total;
+         i0 += (uint64_t)gridDim.x * blockDim.x) {
         // root-major: the tasks of all plans on one hub are pushed together,
         // so the waves of its XCD work on that hub's lists side by side
+        const uint64_t i = i0 + lane;
         const uint32_t pi = (uint32_t)(i % a.n_plans);
         const uint32_t h = (uint32_t)(i / a.n_plans);
         const PlanDesc* P = a.plans + pi;
-        if (P->e < 2) continue;
-        uint32_t r = a.roots ? a.roots[h] : a.hubs[h];
-        if (r >= a.g.n || !in_root_share(r, P->root_share)) continue;
-        uint2 d = a.g.deg[r];
-        if (d.x < P->root_dout || d.y < P->root_din) continue;
-        uint32_t len = level1_len(a.g, P, r);
-        const uint32_t sz = plan_item_size(len, P->e, a.split, a.split_work, a.cap);
-        if (len <= sz) continue;
-        uint32_t nit = (len + sz - 1) / sz;
-        // all tasks of one root go to one queue (one XCD's L2)
-        const uint32_t qu = h % kQueues;
-        const uint32_t qcap = a.qbase[qu + 1] - a.qbase[qu];
-        uint32_t base = atomicAdd(&a.ctl[kCtlSplitCount0 + qu], nit);
-        if (base + nit > qcap) {
-            atomicOr(&a.ctl[kCtlQueueFull], 1u);
-            continue;
+        uint32_t r = 0, len = 0, sz = 1, nit = 0, at = 0;
+        if (i < total && P->e >= 2) {
+            r = a.roots ? a.roots[h] : a.hubs[h];
+            if (r < a.g.n && in_root_share(r, P->root_share)) {
+                const uint2 d = a.g.deg[r];
+                if (d.x >= P->root_dout && d.y >= P->root_din) {
+                    len = level1_len(a.g, P, r);
+                    sz = plan_item_size(len, P->e, a.split, a.split_work, a.cap);
+                    nit = len > sz ? (len + sz - 1) / sz : 0;
+                }
+            }
         }
-        for (uint32_t q = 0; q < nit; q++) {
-            uint32_t lo = q * sz;
-            uint32_t hi = lo + sz < len ? lo + sz : len;
-            a.split_items[a.qbase[qu] + base + q] = make_uint4(pi, r, lo, hi);
+        if (nit) {
+            // all tasks of one root go to one queue (one XCD's L2)
+            const uint32_t qu = h % kQueues;
+            const uint32_t qcap = a.qbase[qu + 1] - a.qbase[qu];
+            const uint32_t base = atomicAdd(&a.ctl[kCtlSplitCount0 + qu], nit);
+            at = a.qbase[qu] + base;
+            if (base + nit > qcap) {
+                atomicOr(&a.ctl[kCtlQueueFull], 1u);
+                nit = 0;
+            }
+        }
+        for (uint64_t m = __ballot(nit > 0); m; m &= m - 1) {
+            const int j = __builtin_ctzll(m);
+            const uint32_t n = uni(__shfl(nit, j, 64)), s = uni(__shfl(sz, j, 64)), l = uni(__shfl(len, j, 64));
+            const uint32_t p = uni(__shfl(pi, j, 64)), root = uni(__shfl(r, j, 64)), to = uni(__shfl(at, j, 64));
+            for (uint32_t q = lane; q < n; q += 64) {
+                const uint32_t lo = q * s, hi = lo + s < l ? lo + s : l;
+                a.split_items[to + q] = make_uint4(p, root, lo, hi);
+            }
         }
     }
 }
