@@ -210,7 +210,7 @@ struct Lds {
     uint32_t* slot_lo;   // [maxc][64]: address of the list or of the dense row (low word)
     uint32_t* slot_hi;   // [maxc][64]: (high word)
     uint32_t* hist;      // [signature masks][64]
-    uint32_t* filt;      // [filt_words]: bit map of a shared list
+    uint32_t* filt;      // [filt_words]: bit map of a shared list, or embeddings to be listed
     uint32_t* st;        // wave state: cur[8], pofs[8], n[8], a donated id range: level, from, to;
                          // the filter's list: address (2 words), length
     uint32_t* mbuf;      // [kMergeChunk]: probe-list chunk of the cooperative merge
@@ -1300,26 +1300,40 @@ __device__ __forceinline__ uint32_t own_count(uint64_t ballot, uint32_t start, u
 }
 
 // Listing: the survivors of a tile pair are whole embeddings (bound levels
-// 0..nb-1 of their parent plus the leaf); one 64-bit atomic per step reserves
-// their rows, written in pattern-vertex order while they fit the capacity.
-__device__ __forceinline__ void write_rows(const Ctx& C, uint32_t nb, uint64_t ma, uint64_t mb, uint32_t ja,
-                                           uint32_t xa, bool oka, uint32_t jb, uint32_t xb, bool okb) {
+// 0..nb-1 of their parent plus the leaf).  They are collected in the wave's LDS
+// (parent and leaf, kListRows of them), and one 64-bit atomic reserves the rows
+// of a collection, written in pattern-vertex order while they fit the
+// capacity.  With one atomic per tile pair the launch was as long as its atomics
+// on that one word: 10.3 M rows of R-MAT 15's triangles 4.4 ms.
+__device__ __forceinline__ void write_rows(const Ctx& C, uint32_t nb, uint32_t& held) {
     const KArgs& a = *C.a;
-    const uint32_t na = (uint32_t)__popcll(ma), nbb = (uint32_t)__popcll(mb);
-    if (na + nbb == 0) return;
+    if (held == 0) return;
+    wave_sync();
     unsigned long long base = 0;
-    if (C.lane == 0) base = atomicAdd(a.list_count, (unsigned long long)(na + nbb));
+    if (C.lane == 0) base = atomicAdd(a.list_count, (unsigned long long)held);
     base = __shfl(base, 0, 64);
     const PlanDesc* P = C.P;
     const uint32_t k = P->k;
-    auto put = [&](unsigned long long row, uint32_t j, uint32_t x) {
-        if (row >= a.list_cap) return;
+    for (uint32_t i = C.lane; i < held; i += 64) {
+        const unsigned long long row = base + i;
+        if (row >= a.list_cap) break;
         uint32_t* out = a.list + row * k;
+        const uint32_t j = C.s.filt[kListRows + i];
         for (uint32_t l = 0; l < nb; l++) out[P->order[l]] = C.s.bound[l * 64 + j];
-        out[P->order[nb]] = x;
-    };
-    if (oka) put(base + rank_below(ma), ja, xa);
-    if (okb) put(base + na + rank_below(mb), jb, xb);
+        out[P->order[nb]] = C.s.filt[i];
+    }
+    held = 0;
+    wave_sync();
+}
+__device__ __forceinline__ void hold_rows(const Ctx& C, uint32_t nb, uint32_t& held, uint64_t m, uint32_t j, uint32_t x,
+                                          bool ok) {
+    if (ok) {
+        const uint32_t at = held + rank_below(m);
+        C.s.filt[at] = x;
+        C.s.filt[kListRows + at] = j;
+    }
+    held += (uint32_t)__popcll(m);
+    if (held + 64 > kListRows) write_rows(C, nb, held);
 }
 
 // Whether a task that has run for a while should look for waiting waves now.
@@ -1463,13 +1477,15 @@ __device__ __forceinline__ uint32_t donate_leaves(Ctx& C, uint32_t lv, uint32_t 
 // Size of descriptor D's candidate set (a leaf signature or a signature mask)
 // for each partial match of the window, the bound nodes it may not hold taken
 // off.  SUM: the sizes' sum (the same for every lane) instead, for plans with
-// one leaf; only then a launch may be listing or merging.
+// one leaf.  Listing and merging are in the roomy kernel with SUM only, which
+// such launches always run: in the 64-VGPR kernel their code costs every launch
+// registers (four motifs on R-MAT 16 20.1 ms with it).
 template <bool SUM, bool ROOMY>
 __device__ __forceinline__ unsigned long long leaf_set(Ctx& C, const LK& D, uint32_t nb, uint32_t p, bool pv,
                                                        uint32_t same) {
     const KArgs& a = *C.a;
     const uint32_t lane = C.lane;
-    const bool listing = SUM && a.list != nullptr;
+    const bool listing = SUM && ROOMY && a.list != nullptr;
     const uint32_t shared = shared_cons(D, same);
     uint32_t flen, brow, bskip;
     uint32_t len = phase_a<true>(C, D, nb, p, pv, false, shared, flen, brow, bskip);
@@ -1480,7 +1496,7 @@ __device__ __forceinline__ unsigned long long leaf_set(Ctx& C, const LK& D, uint
     // one leaf whose set is a base list and one probe list: balanced big pairs
     // leave the flattened pass for the cooperative merge
     bool big = false;
-    if (SUM && a.merge_min != 0xFFFFFFFFu && pv && !listing) {
+    if (SUM && ROOMY && a.merge_min != 0xFFFFFFFFu && pv && !listing) {
         uint32_t nprobe = 0, pl = 0;
         for (uint32_t c = 0; c < ns; c++)
             if (C.s.slot_len[c * 64 + lane] != kSkip) {
@@ -1492,7 +1508,7 @@ __device__ __forceinline__ unsigned long long leaf_set(Ctx& C, const LK& D, uint
             big = mn >= a.merge_min && (uint64_t)mx <= (uint64_t)a.merge_ratio * mn;
         }
     }
-    uint64_t bigmask = SUM ? __ballot(big) : 0ull;
+    uint64_t bigmask = SUM && ROOMY ? __ballot(big) : 0ull;
     // long base lists leave the flattened pass too (listing stays flattened)
     Par P1 = parent_view(C, ns, len);
     const bool wd = len >= kWideMin && !big && !listing && !D.deg_check;
@@ -1509,7 +1525,7 @@ __device__ __forceinline__ unsigned long long leaf_set(Ctx& C, const LK& D, uint
     const uint32_t start = incl - len;
     wave_sync();
     unsigned long long lin = 0;
-    uint32_t h = 0, carry = 0;
+    uint32_t h = 0, carry = 0, held = 0;
     // two tiles per step
     for (uint32_t t0 = 0; t0 < T; t0 += 128) {
         const uint32_t ga = t0 + lane, gb = t0 + 64 + lane;
@@ -1528,11 +1544,15 @@ __device__ __forceinline__ unsigned long long leaf_set(Ctx& C, const LK& D, uint
         const uint64_t ma = __ballot(oka), mb = __ballot(okb);
         if (SUM) {
             lin += (unsigned long long)(__popcll(ma) + __popcll(mb));
-            if (listing) write_rows(C, nb, ma, mb, ja, xa, oka, jb, xb, okb);
+            if (listing) {
+                hold_rows(C, nb, held, ma, ja, xa, oka);
+                hold_rows(C, nb, held, mb, jb, xb, okb);
+            }
         } else if (owns) {
             h += own_count(ma, start, len, t0) + own_count(mb, start, len, t0 + 64);
         }
     }
+    if (SUM && listing) write_rows(C, nb, held);
     auto add = [&](uint32_t j, uint32_t n) {
         if (SUM) lin += n;
         else h += lane == j ? n : 0u;
@@ -1560,7 +1580,7 @@ __device__ __forceinline__ unsigned long long leaf_set(Ctx& C, const LK& D, uint
     }
     wave_sync();
     // balanced big pairs, one partial match at a time
-    for (; SUM && bigmask; bigmask &= bigmask - 1) {
+    for (; SUM && ROOMY && bigmask; bigmask &= bigmask - 1) {
         const uint32_t j = (uint32_t)__builtin_ctzll(bigmask);
         const uint32_t blen = uni(C.s.base_len[j]);
         uint32_t pc = 0;
@@ -1675,12 +1695,12 @@ __device__ __forceinline__ void count_leaves(Ctx& C, uint32_t lv, uint32_t npref
                 if (l > 0) idx = F.parent[idx];
             }
         }
-        const uint32_t same = ROOMY && a.filt_words ? same_levels(C, nb, pv) : 0u;
+        const uint32_t same = ROOMY && a.filt_words && !a.list ? same_levels(C, nb, pv) : 0u;
         if (NONLIN) {
             leaf_masks<ROOMY>(C, nb, p, pv, same);
         } else {
             unsigned long long v = 0;
-            if (a.list == nullptr && S0.n_cons == 1 && S0.reuse == kNoReuse) {
+            if ((!ROOMY || a.list == nullptr) && S0.n_cons == 1 && S0.reuse == kNoReuse) {
                 v = leaf_list(C, S0, nb, pv);
             } else {
                 v = leaf_set<true, ROOMY>(C, S0, nb, p, pv, same);
@@ -2267,7 +2287,8 @@ hipError_t launch_count(const InitArgs* inits, int n_inits, const KArgs& a, uint
         if (e != hipSuccess) return e;
     }
     // the whole kernel in registers when the launch asks for few enough waves
-    const bool roomy = n_blocks <= (uint64_t)a.n_cu * kRoomyBlocksPerCu;
+    // (listing and merging are in that kernel only)
+    const bool roomy = n_blocks <= (uint64_t)a.n_cu * kRoomyBlocksPerCu || a.list || a.merge_min != 0xFFFFFFFFu;
     if (a.nonlinear && roomy)
         hipLaunchKernelGGL((count_kernel<true, kRoomyBlocksPerCu>), dim3(n_blocks), dim3(kBlockThreads), lds, stream, a);
     else if (a.nonlinear)

@@ -87,6 +87,7 @@ struct DevGraph {
 };
 
 constexpr uint32_t kLdsPerCu = 160u << 10;  // gfx950
+constexpr uint32_t kListRows = 512;  // embeddings a wave holds before it writes them out (listing)
 constexpr uint32_t kFilterMinWords = 256, kFilterMaxWords = 2048;  // a wave's shared-list filter
 constexpr uint32_t kNoRows = 0xFFFFFFFFu;
 constexpr uint32_t kRowLen = 0xFFFFFFFEu;  // probe-list length marker: test a dense row
@@ -123,7 +124,8 @@ struct KArgs {
     uint32_t lds_words;         // LDS words per wave
     uint32_t lds_rows;          // bound / ancestor rows (largest enumerated depth)
     uint32_t maxc;              // largest constraint count over plans and signatures
-    uint32_t filt_words;        // LDS words of a wave's shared-list bit map (a power of two; 0: none)
+    uint32_t filt_words;        // LDS words of a wave's shared-list bit map (a power of two; 0: none); in a
+                                // listing launch, of the embeddings it holds
     uint32_t nonlinear;         // some plan counts a leaf group of several vertices
     uint32_t n_cu;              // compute units of the device (picks the register budget)
     uint32_t merge_min;         // cooperative merge thresholds

@@ -188,6 +188,11 @@ int make_layout(const xm_graph_t* g, uint32_t n_plans, const xm_plan_t* const* p
     const bool merging = L.merge_min != 0xFFFFFFFFu;
     L.filt_words = 0;
     L.lds_words = xm::lds_words_for(L.e_max, L.maxc, masks, merging);
+    const bool listing = full_opts && o->list_dev;
+    if (listing) {
+        L.filt_words = 2 * xm::kListRows;
+        L.lds_words += L.filt_words;
+    }
     if (L.waves_per_cu == 0) {
         // as many waves as can be resident at once: the kernel is persistent.
         // When LDS leaves room for fewer than 6 blocks of the 64-VGPR kernel,
@@ -203,7 +208,7 @@ int make_layout(const xm_graph_t* g, uint32_t n_plans, const xm_plan_t* const* p
         L.waves_per_cu = (uint32_t)std::max(1, std::min(bpc, 8)) * xm::kWavesPerBlock;
     }
     const uint32_t blocks = (L.waves_per_cu + xm::kWavesPerBlock - 1) / xm::kWavesPerBlock;
-    if (!merging && !(full_opts && o->list_dev) && blocks <= (uint32_t)xm::kRoomyBlocksPerCu) {
+    if (!merging && !listing && blocks <= (uint32_t)xm::kRoomyBlocksPerCu) {
         // the largest bit map that the resident blocks' LDS leaves room for, at
         // most one bit a node
         const size_t room =
