@@ -686,9 +686,9 @@ __device__ __forceinline__ void wide_scan(const Ctx& C, const LK& D, uint32_t in
 
 // Whether bound node y of this lane's partial match lies in the lane's base
 // list and passes all its probes: then a flattened pass without injectivity
-// counted it once.
-__device__ __forceinline__ bool bound_in_set(const Ctx& C, uint32_t ns, uint32_t y) {
-    const uint32_t lane = C.lane;
+// counted it once.  (at: the lane whose base list and probes they are.)
+__device__ __forceinline__ bool bound_in_set(const Ctx& C, uint32_t ns, uint32_t y, uint32_t at) {
+    const uint32_t lane = at;
     const uint32_t len = C.s.base_len[lane];
     if (!contains(join_ptr(C.s.base_lo[lane], C.s.base_hi[lane]), len, y)) return false;
     for (uint32_t k = 0; k < ns; k++)
@@ -1487,12 +1487,19 @@ __device__ __forceinline__ unsigned long long leaf_set(Ctx& C, const LK& D, uint
     const uint32_t lane = C.lane;
     const bool listing = SUM && ROOMY && a.list != nullptr;
     const uint32_t shared = shared_cons(D, same);
+    // When every constraint is on a node that the window shares (and so is the
+    // reused set), all its partial matches have the same set: lane 0 measures
+    // it for all, and only the bound nodes are looked up lane by lane.
+    // Without and with it: C5 + chord on R-MAT 20 61 and 50 ms, 96 plans on R-MAT
+    // 22 324 and 300 ms.
+    const bool once = ROOMY && !listing && D.n_cons > 0 && shared == (1u << D.n_cons) - 1u && D.gt == 0 &&
+                      (D.reuse == kNoReuse || (~same & ((1u << D.reuse) - 1u)) == 0);
     uint32_t flen, brow, bskip;
-    uint32_t len = phase_a<true>(C, D, nb, p, pv, false, shared, flen, brow, bskip);
+    uint32_t len = phase_a<true>(C, D, nb, p, pv && !(once && lane > 0), false, shared, flen, brow, bskip);
     const uint32_t ns = n_slots(D);
     Filter flt{};
     flt.vk = kSkip;
-    if (ROOMY && shared) use_filter(C, D, nb, shared, flen, len, flt);
+    if (ROOMY && shared && a.filt_words) use_filter(C, D, nb, shared, flen, len, flt);
     // one leaf whose set is a base list and one probe list: balanced big pairs
     // leave the flattened pass for the cooperative merge
     bool big = false;
@@ -1571,10 +1578,15 @@ __device__ __forceinline__ unsigned long long leaf_set(Ctx& C, const LK& D, uint
         const uint32_t j = (uint32_t)__builtin_ctzll(wide);
         add(j, wide_count(C, D, nb, ns, j));
     }
+    if (once) {
+        h = pv ? uni(h) : 0u;
+        if (SUM) lin *= (unsigned long long)__popcll(__ballot(pv));
+        wave_sync();
+    }
     // the bound nodes the set may not contain were counted if present
     for (uint32_t b = 0; b < nb && !listing; b++) {
         if (!((D.inj >> b) & 1u)) continue;
-        const bool hit = pv && !big && bound_in_set(C, ns, C.s.bound[b * 64 + lane]);
+        const bool hit = pv && !big && bound_in_set(C, ns, C.s.bound[b * 64 + lane], once ? 0u : lane);
         if (SUM) lin -= (unsigned long long)__popcll(__ballot(hit));
         else h -= hit ? 1u : 0u;
     }
@@ -1695,7 +1707,7 @@ __device__ __forceinline__ void count_leaves(Ctx& C, uint32_t lv, uint32_t npref
                 if (l > 0) idx = F.parent[idx];
             }
         }
-        const uint32_t same = ROOMY && a.filt_words && !a.list ? same_levels(C, nb, pv) : 0u;
+        const uint32_t same = ROOMY && !a.list ? same_levels(C, nb, pv) : 0u;
         if (NONLIN) {
             leaf_masks<ROOMY>(C, nb, p, pv, same);
         } else {

@@ -144,3 +144,26 @@ def test_short_lists_against_a_shared_list(xa, n):
         for reduced in (True, False):
             assert xa.count(G, [xa.Plan(p, reduced=reduced, graph=G) for p in pats], **opts) == want
         assert xa.count(G, [xa.Plan(p, graph=G, symmetry="above") for p in pats[:3]], **opts) == want[:3]
+
+
+@pytest.mark.parametrize("n, deg", [(40, 12), (300, 20), (300, 90)])
+def test_sets_shared_by_a_whole_window(xa, n, deg):
+    """Leaf groups with a leaf whose neighbours are bound early, so windows of
+    partial matches share its candidate set (measured once): windows smaller
+    than a wave, cut by slices, and sets below and above the scan lengths.  The
+    last pattern has one leaf, next to a plan with several in the same launch."""
+    rng = np.random.default_rng(n + deg)
+    u, v = rng.integers(0, n, (2, n * deg))
+    g = xmgen.from_arcs(n, u, v)
+    P = xmgen.Pattern
+    pats = [xmgen.named("tt4p"), P(4, ((0, 1), (0, 2), (1, 2), (3, 0), (3, 1))),
+            P(5, ((0, 1), (1, 2), (0, 3), (1, 3), (1, 4), (4, 0), (2, 0))) if deg < 100 else xmgen.named("c4"),
+            P(4, ((0, 1), (1, 2), (2, 3), (3, 1)))]
+    want = [oracle.count(g, p) for p in pats]
+    G = xa.Graph(g, row_min=64)
+    for opts in (dict(), dict(cap=64, split=64), dict(cap=100, split=64, waves_per_cu=4)):
+        print("[case]", n, deg, opts, flush=True)
+        assert xa.count(G, [xa.Plan(p, graph=G) for p in pats], **opts) == want
+        for p, w in zip(pats, want):
+            assert xa.count(G, [xa.Plan(p, graph=G)], **opts) == [w]
+            assert xa.count(G, [xa.Plan(p, graph=G, symmetry="below")], **opts) == [w]
