@@ -221,7 +221,11 @@ int xm_plan_work(uint32_t n, const uint32_t* out_off, const uint32_t* out_adj,
  * a binary search otherwise (tests stop at the first failing list), and the
  * partial matches written and their ancestor chains read back.  It assumes
  * every window holds whole candidate sets (no hub sub-ranges or donated
- * prefixes).  out[XM_TRAFFIC_WORDS]:
+ * prefixes).  It prices every test by itself: the kernel reads less where it
+ * intersects the dense heads of two rows word by word, tests short lists
+ * against a bit map in LDS, or measures a set once for a window that shares
+ * it, so the total is the work a launch gets through, not its traffic.
+ * out[XM_TRAFFIC_WORDS]:
  *   [0] base elements scanned (4 B each)     [1] offset pairs read (8 B)
  *   [2] degree classes read (1 B)             [3] dense-row words tested (4 B)
  *   [4] sorted-list searches                  [5] words those searches load (4 B)

@@ -525,9 +525,9 @@ struct Filter {
 // slot as a dense-row bit test or a sorted-list search.  oka / okb: in =
 // element valid, out = element passes.
 template <bool FILT>
-__device__ __forceinline__ void check_pair(const Ctx& C, const LK& D, const Filter& flt, uint32_t inj, uint32_t lv, uint32_t ns,
-                                           uint32_t ja, uint32_t xa, bool& oka, uint32_t jb, uint32_t xb,
-                                           bool& okb) {
+__device__ __forceinline__ void check_pair(const Ctx& C, const LK& D, const Filter& flt, uint32_t inj, uint32_t lv,
+                                           uint32_t ns, uint32_t ja, uint32_t xa, bool& oka, uint32_t jb,
+                                           uint32_t xb, bool& okb) {
     const DevGraph& g = C.a->g;
     bool fa = false, fb = false;  // the filter decides the probe in slot vk
     if (FILT && flt.lanes) {
@@ -1114,7 +1114,8 @@ __device__ __forceinline__ uint32_t expand(Ctx& C, uint32_t lv) {
     bool cut = false;
     if (uni(st[24]) == lv && uni(st[26]) != kSkip && pv) {
         // a donated id range: its part of the sorted base list
-        const uint32_t* base = reinterpret_cast<const uint32_t*>(((uint64_t)C.s.base_hi[lane] << 32) | C.s.base_lo[lane]);
+        const uint64_t at = ((uint64_t)C.s.base_hi[lane] << 32) | C.s.base_lo[lane];
+        const uint32_t* base = reinterpret_cast<const uint32_t*>(at);
         const uint32_t lo = count_lt(base, len, uni(st[25])), hi = count_lt(base, len, uni(st[26]));
         const uint64_t bv = reinterpret_cast<uint64_t>(base + lo);
         cut = hi - lo < len;

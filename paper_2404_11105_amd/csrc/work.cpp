@@ -20,7 +20,10 @@
 // the partial matches written to the level buffers and the ancestor chains
 // read back.  It assumes every window holds whole candidate sets (no hub
 // sub-ranges, donated prefixes or window slices), as in a launch whose
-// tasks are whole roots.
+// tasks are whole roots.  Every test is priced by itself: where the kernel
+// intersects the dense heads of two rows word by word, tests short lists
+// against a bit map in LDS or measures a set once for a window that shares it,
+// it reads less than this account.
 //
 // Both are statistics for roofline accounting: no count is returned.
 #include <hip/hip_runtime.h>
