@@ -278,12 +278,12 @@ typedef struct xm_count_opts {
     uint32_t cap;           /* per-level candidate buffer entries (default 4096,
                                at least split) */
     uint32_t waves_per_cu;  /* resident waves per compute unit, 4..32 (default:
-                               as many as LDS allows, at most 32; when that is
-                               fewer than 24, or no list of the graph has more
-                               than 64 elements, 12 or as many as LDS allows).
+                               24, or when LDS allows fewer, or no list of the
+                               graph has more than 64 elements, 12 or as many as
+                               LDS allows; at most 24 are launched).
                                Launches of at most 12 waves per CU run a build
                                of the count kernel that keeps all its state in
-                               registers; larger ones a build limited to 64
+                               registers; larger ones a build limited to 80
                                VGPRs that spills some of it. */
     /* root subset: device array of n_roots node ids (< n, distinct); when
        non-NULL only these nodes are tried as images of the plan's start

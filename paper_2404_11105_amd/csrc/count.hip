@@ -1479,7 +1479,7 @@ __device__ __forceinline__ uint32_t donate_leaves(Ctx& C, uint32_t lv, uint32_t 
 // for each partial match of the window, the bound nodes it may not hold taken
 // off.  SUM: the sizes' sum (the same for every lane) instead, for plans with
 // one leaf.  Listing and merging are in the roomy kernel with SUM only, which
-// such launches always run: in the 64-VGPR kernel their code costs every launch
+// such launches always run: in the 80-VGPR kernel their code costs every launch
 // registers (four motifs on R-MAT 16 20.1 ms with it).
 template <bool SUM, bool ROOMY>
 __device__ __forceinline__ unsigned long long leaf_set(Ctx& C, const LK& D, uint32_t nb, uint32_t p, bool pv,
@@ -1797,10 +1797,12 @@ __device__ __forceinline__ void explore(Ctx& C, uint32_t n0, uint32_t start) {
     }
 }
 
-// Two register budgets.  MINB resident blocks per CU: 8 (8 waves per SIMD,
-// 64 VGPRs, some state spilled to scratch) for launches of more than
-// kRoomyBlocksPerCu blocks per CU, and kRoomyBlocksPerCu (3 waves per SIMD,
-// the whole kernel in registers) for launches of at most that many.
+// Two register budgets.  MINB resident blocks per CU: kFullBlocksPerCu (6 waves
+// per SIMD, 80 VGPRs, some state spilled to scratch) for launches of more than
+// kRoomyBlocksPerCu blocks per CU, and kRoomyBlocksPerCu (3 waves per SIMD, the
+// whole kernel in registers) for launches of at most that many.  The larger one
+// at 8 / 7 / 6 blocks: four motifs on R-MAT 16 18.2 / 18.5 / 17.8 ms, unreduced
+// 152 / 152 / 144 ms, a tenth of the roots 38.6 / 38.6 / 37.6 ms.
 template <bool NONLIN, int MINB>
 __global__ void __launch_bounds__(kBlockThreads, MINB) count_kernel(KArgs a) {
     constexpr bool ROOMY = MINB <= kRoomyBlocksPerCu;
@@ -2227,9 +2229,9 @@ int count_blocks_per_cu(bool nonlin, size_t lds_bytes) {
     int nb = 0;
     hipError_t e;
     if (nonlin)
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, count_kernel<true, 8>, kBlockThreads, lds_bytes);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, count_kernel<true, kFullBlocksPerCu>, kBlockThreads, lds_bytes);
     else
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, count_kernel<false, 8>, kBlockThreads, lds_bytes);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, count_kernel<false, kFullBlocksPerCu>, kBlockThreads, lds_bytes);
     return e == hipSuccess ? nb : 0;
 }
 
@@ -2305,11 +2307,11 @@ hipError_t launch_count(const InitArgs* inits, int n_inits, const KArgs& a, uint
     if (a.nonlinear && roomy)
         hipLaunchKernelGGL((count_kernel<true, kRoomyBlocksPerCu>), dim3(n_blocks), dim3(kBlockThreads), lds, stream, a);
     else if (a.nonlinear)
-        hipLaunchKernelGGL((count_kernel<true, 8>), dim3(n_blocks), dim3(kBlockThreads), lds, stream, a);
+        hipLaunchKernelGGL((count_kernel<true, kFullBlocksPerCu>), dim3(n_blocks), dim3(kBlockThreads), lds, stream, a);
     else if (roomy)
         hipLaunchKernelGGL((count_kernel<false, kRoomyBlocksPerCu>), dim3(n_blocks), dim3(kBlockThreads), lds, stream, a);
     else
-        hipLaunchKernelGGL((count_kernel<false, 8>), dim3(n_blocks), dim3(kBlockThreads), lds, stream, a);
+        hipLaunchKernelGGL((count_kernel<false, kFullBlocksPerCu>), dim3(n_blocks), dim3(kBlockThreads), lds, stream, a);
     if (ev_stop) {
         hipError_t e = hipEventRecord(ev_stop, stream);
         if (e != hipSuccess) return e;

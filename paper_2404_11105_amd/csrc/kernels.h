@@ -164,6 +164,8 @@ constexpr uint32_t kMaxPieces = 4096;  // sub-range tasks per root and plan, at 
 // launches of at most this many resident blocks per CU use the count kernel
 // compiled for that occupancy, which keeps all its state in registers
 constexpr int kRoomyBlocksPerCu = 3;
+// and the others the kernel compiled for this many (more blocks are not launched)
+constexpr int kFullBlocksPerCu = 6;
 
 // The base list of a level below the first (and of a leaf pass): the
 // shortest constraint list, except that when the shortest belongs to an

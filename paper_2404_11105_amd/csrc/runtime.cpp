@@ -195,7 +195,7 @@ int make_layout(const xm_graph_t* g, uint32_t n_plans, const xm_plan_t* const* p
     }
     if (L.waves_per_cu == 0) {
         // as many waves as can be resident at once: the kernel is persistent.
-        // When LDS leaves room for fewer than 6 blocks of the 64-VGPR kernel,
+        // When LDS leaves room for fewer than 6 blocks of the 80-VGPR kernel,
         // its extra occupancy does not pay for its spills: take the kernel
         // that keeps everything in registers at its kRoomyBlocksPerCu blocks
         // (measured: 256 plans on R-MAT 22 1,340 ms at 3 blocks against
@@ -204,8 +204,8 @@ int make_layout(const xm_graph_t* g, uint32_t n_plans, const xm_plan_t* const* p
         // lists, which only that kernel has, saves more than the waves hide
         // (four motifs on 2,000 nodes 288 us at 8 blocks, 256 us at 3).
         int bpc = xm::count_blocks_per_cu(L.nonlinear, (size_t)L.lds_words * 4 * xm::kWavesPerBlock);
-        if (bpc < 6 || g->n_hubs == 0) bpc = std::min(bpc, xm::kRoomyBlocksPerCu);
-        L.waves_per_cu = (uint32_t)std::max(1, std::min(bpc, 8)) * xm::kWavesPerBlock;
+        if (bpc < xm::kFullBlocksPerCu || g->n_hubs == 0) bpc = std::min(bpc, xm::kRoomyBlocksPerCu);
+        L.waves_per_cu = (uint32_t)std::max(1, std::min(bpc, xm::kFullBlocksPerCu)) * xm::kWavesPerBlock;
     }
     const uint32_t blocks = (L.waves_per_cu + xm::kWavesPerBlock - 1) / xm::kWavesPerBlock;
     if (!merging && !listing && blocks <= (uint32_t)xm::kRoomyBlocksPerCu) {
@@ -312,8 +312,10 @@ int make_layout(const xm_graph_t* g, uint32_t n_plans, const xm_plan_t* const* p
         // starts no more blocks than its items and those waiters need
         const uint64_t n_src = (o && o->roots_dev) ? o->n_roots : g->n;
         const uint64_t tasks = (n_src + L.chunk - 1) / L.chunk * n_plans + items + xm::kMaxWaiters;
-        L.launch_blocks =
-            (uint32_t)std::min<uint64_t>(L.n_blocks, (tasks + xm::kWavesPerBlock - 1) / xm::kWavesPerBlock);
+        // (and no more than can be resident at once)
+        L.launch_blocks = (uint32_t)std::min<uint64_t>(
+            std::min<uint64_t>(L.n_blocks, (uint64_t)g->n_cu * xm::kFullBlocksPerCu),
+            (tasks + xm::kWavesPerBlock - 1) / xm::kWavesPerBlock);
     }
     L.qbase[0] = 0;
     for (uint32_t q = 0; q < xm::kQueues; q++) L.qbase[q + 1] = L.qbase[q] + (uint32_t)qc[q];
