@@ -1502,9 +1502,10 @@ __device__ __forceinline__ unsigned long long leaf_set(Ctx& C, const LK& D, uint
     flt.vk = kSkip;
     if (ROOMY && shared && a.filt_words) use_filter(C, D, nb, shared, flen, len, flt);
     // one leaf whose set is a base list and one probe list: balanced big pairs
-    // leave the flattened pass for the cooperative merge
+    // leave the flattened pass for the cooperative merge (a set measured once is
+    // scanned: a merge settles one partial match's bound nodes only)
     bool big = false;
-    if (SUM && ROOMY && a.merge_min != 0xFFFFFFFFu && pv && !listing) {
+    if (SUM && ROOMY && a.merge_min != 0xFFFFFFFFu && pv && !listing && !once) {
         uint32_t nprobe = 0, pl = 0;
         for (uint32_t c = 0; c < ns; c++)
             if (C.s.slot_len[c * 64 + lane] != kSkip) {
