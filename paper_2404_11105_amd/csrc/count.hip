@@ -29,6 +29,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "donate.h"
 #include "kernels.h"
 #include "u128.h"
 
@@ -1360,33 +1361,35 @@ __device__ __forceinline__ bool time_to_look(Ctx& C) {
 // (with no such bound every running wave donated half of its work each time,
 // 260,000 tasks a launch, and taking them took seconds).
 //
-// Slots that may be donated now (0: none); `tail` becomes the queue's tail.
-__device__ __forceinline__ uint32_t donation_room(const Ctx& C, uint32_t& tail) {
+// Tasks that may be donated now (0: none); `tail` becomes the queue's tail, and
+// `head` its head or an earlier one.
+__device__ __forceinline__ uint32_t donation_room(const Ctx& C, uint32_t& head, uint32_t& tail) {
     uint32_t v = 0;
     if (C.lane == 0) v = __atomic_load_n(&C.a->ctl[kCtlIdle], __ATOMIC_RELAXED);
     const uint32_t idle = uni(__shfl(v, 0, 64));
-    tail = 0;
+    head = tail = 0;
     if (idle == 0) return 0;
     if (C.lane < 2) v = __atomic_load_n(&C.a->ctl[C.lane ? kCtlDonTail : kCtlDonHead], __ATOMIC_RELAXED);
     tail = uni(__shfl(v, 1, 64));
-    const uint32_t head = uni(__shfl(v, 0, 64));
+    head = uni(__shfl(v, 0, 64));
     return idle > tail - head ? idle - (tail - head) : 0u;
 }
 // Reserve k slots behind the tail that donation_room saw.  One try: thousands of
 // waves may look at the same time, and retrying against each other took longer
 // than the work they had (a failed try comes back with the next look).
-__device__ __forceinline__ uint32_t reserve_slots(Ctx& C, uint32_t k, uint32_t tail) {
+__device__ __forceinline__ uint32_t reserve_slots(Ctx& C, uint32_t k, uint32_t head, uint32_t tail) {
     const KArgs& a = *C.a;
     uint32_t base = kSkip;
-    if (C.lane == 0 && tail + k <= a.don_cap && atomicCAS(&a.ctl[kCtlDonTail], tail, tail + k) == tail) base = tail;
+    if (C.lane == 0 && don_fits(head, tail, k, a.don_cap) && atomicCAS(&a.ctl[kCtlDonTail], tail, tail + k) == tail)
+        base = tail;
     base = uni(__shfl(base, 0, 64));
     if (base != kSkip) C.donated = true;
     return base;
 }
 // One donated task: level l below entry idx of level l-1, ids in [xlo, xhi).
-__device__ __forceinline__ void donate(Ctx& C, uint32_t slot, uint32_t l, uint32_t idx, uint32_t xlo, uint32_t xhi) {
+__device__ __forceinline__ void donate(Ctx& C, uint32_t seq, uint32_t l, uint32_t idx, uint32_t xlo, uint32_t xhi) {
     const KArgs& a = *C.a;
-    uint32_t* ent = a.don + (uint64_t)slot * kDonWords;
+    uint32_t* ent = a.don + (uint64_t)don_slot(seq, a.don_cap) * kDonWords;
     // Relaxed atomics go past the XCD's L2 by themselves; a release fence would
     // write that whole L2 back and the taker's acquire would empty its own (a
     // launch with 50,000 donated tasks spent most of a second on it).  The
@@ -1401,7 +1404,7 @@ __device__ __forceinline__ void donate(Ctx& C, uint32_t slot, uint32_t l, uint32
     put(kDonWords - 1, xhi);
     put(0, C.pi | (l << 16));
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    put(1, 1u);
+    put(1, don_published(seq, a.don_cap));
 }
 
 // At the shallowest level l >= 2 with at least two parents at level l-1 not yet
@@ -1409,8 +1412,8 @@ __device__ __forceinline__ void donate(Ctx& C, uint32_t slot, uint32_t l, uint32
 // drops them from its window.
 __device__ __forceinline__ void donate_parents(Ctx& C, uint32_t start, uint32_t lv) {
     uint32_t* st = C.s.st;
-    uint32_t tail;
-    const uint32_t room = donation_room(C, tail);
+    uint32_t head, tail;
+    const uint32_t room = donation_room(C, head, tail);
     if (room == 0) return;
     for (uint32_t l = (start > 2 ? start : 2); l <= lv; l++) {
         const uint32_t n = uni(st[16 + l - 1]);
@@ -1420,7 +1423,7 @@ __device__ __forceinline__ void donate_parents(Ctx& C, uint32_t start, uint32_t 
         uint32_t k = (n - first) / 2;
         k = k < 64 ? k : 64;
         k = k < room ? k : room;
-        const uint32_t base = reserve_slots(C, k, tail);
+        const uint32_t base = reserve_slots(C, k, head, tail);
         if (base == kSkip) return;  // no room: keep the work
         if (C.lane < k) donate(C, base + C.lane, l, n - k + C.lane, 0, kSkip);
         if (C.lane == 0) st[16 + l - 1] = n - k;
@@ -1438,8 +1441,8 @@ __device__ __forceinline__ uint32_t donate_leaves(Ctx& C, uint32_t lv, uint32_t 
     if (n < from + 2 * kDonatePiece) return n;
     const uint64_t pieces = (uint64_t)each * ((n - from) / 2) / kDonateWork;
     if (pieces == 0) return n;
-    uint32_t tail;
-    uint32_t room = donation_room(C, tail);
+    uint32_t head, tail;
+    uint32_t room = donation_room(C, head, tail);
     if (room == 0) return n;
     room = room < 64 ? room : 64;
     room = room < pieces ? room : (uint32_t)pieces;
@@ -1468,7 +1471,7 @@ __device__ __forceinline__ uint32_t donate_leaves(Ctx& C, uint32_t lv, uint32_t 
     }
     const uint64_t m = __ballot(b < e);
     if (!m) return n;
-    const uint32_t base = reserve_slots(C, (uint32_t)__popcll(m), tail);
+    const uint32_t base = reserve_slots(C, (uint32_t)__popcll(m), head, tail);
     if (base == kSkip) return n;
     if (b < e) donate(C, base + rank_below(m), lv, q, F.node[b], F.node[e - 1] + 1u);
     wave_sync();
@@ -1951,11 +1954,10 @@ __global__ void __launch_bounds__(kBlockThreads, MINB) count_kernel(KArgs a) {
                 if (wait && ln == 0) atomicAdd(&a.ctl[kCtlIdle], 1u);
                 uint32_t nap = 1;
                 for (uint32_t polls = 0; polls < kIdlePolls; polls++) {
-                    // queue entries [head, tail): ready words 0 reserved, 1 published,
-                    // 2 claimed.  A waiter tries an entry of its own choosing, so
-                    // the claims spread over the entries (one CAS on the head by
-                    // all waiters took ~7 us a task); now and then it is the head,
-                    // which moves past claimed entries.
+                    // queue entries [head, tail).  A waiter tries an entry of its own
+                    // choosing, so the claims spread over the entries (one CAS on
+                    // the head by all waiters took ~7 us a task); now and then it is
+                    // the head, which moves past entries that were read.
                     uint32_t h = 0, t = 0, got = kSkip;
                     if (ln == 0) {
                         h = __atomic_load_n(&a.ctl[kCtlDonHead], __ATOMIC_RELAXED);
@@ -1963,12 +1965,14 @@ __global__ void __launch_bounds__(kBlockThreads, MINB) count_kernel(KArgs a) {
                         if (h < t) {
                             const uint32_t r = (uint32_t)(gw * 2654435761u + polls * 40503u) >> 9;
                             const uint32_t s = (r & 3u) ? h + r % (t - h) : h;
-                            uint32_t* const word = &a.don[(uint64_t)s * kDonWords + 1];
+                            uint32_t* const word = &a.don[(uint64_t)don_slot(s, a.don_cap) * kDonWords + 1];
+                            const uint32_t pub = don_published(s, a.don_cap);
                             const uint32_t seen = __atomic_load_n(word, __ATOMIC_RELAXED);
-                            if (seen == 1u && atomicCAS(word, 1u, 2u) == 1u) got = s;
-                            // move the head past claimed entries
+                            if (seen == pub && atomicCAS(word, pub, pub + 1u) == pub) got = s;
                             for (uint32_t i = 0; s == h && h < t && i < 8; i++) {
-                                if (__atomic_load_n(&a.don[(uint64_t)h * kDonWords + 1], __ATOMIC_RELAXED) != 2u) break;
+                                if (__atomic_load_n(&a.don[(uint64_t)don_slot(h, a.don_cap) * kDonWords + 1],
+                                                    __ATOMIC_RELAXED) != don_read(h, a.don_cap))
+                                    break;
                                 atomicCAS(&a.ctl[kCtlDonHead], h, h + 1);
                                 h++;
                             }
@@ -2035,7 +2039,7 @@ __global__ void __launch_bounds__(kBlockThreads, MINB) count_kernel(KArgs a) {
         } else if (kind == 3) {
             // a donated prefix: bind levels 0..d-1 as single entries and explore from
             // level d, within the id range that came with it
-            uint32_t* ent = a.don + (uint64_t)item * kDonWords;
+            uint32_t* ent = a.don + (uint64_t)don_slot(item, a.don_cap) * kDonWords;
             asm volatile("" ::: "memory");  // (its words are read past L2, after the claim)
             const uint32_t head = uni(__atomic_load_n(&ent[0], __ATOMIC_RELAXED));
             set_plan(head & 0xFFFFu);
@@ -2051,6 +2055,9 @@ __global__ void __launch_bounds__(kBlockThreads, MINB) count_kernel(KArgs a) {
                 C.s.st[25] = __atomic_load_n(&ent[kDonWords - 2], __ATOMIC_RELAXED);
                 C.s.st[26] = __atomic_load_n(&ent[kDonWords - 1], __ATOMIC_RELAXED);
             }
+            // every word has arrived: the slot is free for another task
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (C.lane == 0) __atomic_store_n(&ent[1], don_read(item, a.don_cap), __ATOMIC_RELAXED);
             n0 = 1;
         } else {
             // interleave plans so that all of them start on the low (hub) ids

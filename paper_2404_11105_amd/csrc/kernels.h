@@ -22,8 +22,13 @@ constexpr uint32_t kActiveLines = 64;  // one per lane of a waiting wave
 constexpr uint32_t kMaxWaiters = 256;  // waves that wait for donated work; the others leave
 constexpr uint32_t kDonWords = 9;  // donated task: plan | depth << 16, ready flag, prefix nodes [5], id range [2]
 static_assert(kMaxK - 1 <= 6, "a donated prefix has at most 5 nodes (levels 0..e-2, e <= 6)");
-constexpr uint32_t kDonCap = 1u << 18;  // donated-task slots per launch
-constexpr uint32_t kDonCapStatic = 3u << 12;  // ... in launches on the static scratch array
+// Donated-task slots: about as many tasks are queued as waves wait, so these are
+// several times what is in use at a time.  (2^18 slots that were used once each
+// ran out after a second or so of donated work, and what was left stayed with
+// whoever held it: 5-cycle with a chord, unreduced, one hub root of R-MAT 17,
+// 6.3 s with them, 1.7 s with these; and every launch cleared them all.)
+constexpr uint32_t kDonCap = 1u << 12;
+constexpr uint32_t kDonCapStatic = 1u << 11;  // ... in launches on the static scratch array (powers of two)
 // Copies of the count totals: 32 for up to 64 plans, then fewer (plans spread
 // the updates by themselves); a copy starts on a cache line of its own.
 inline uint32_t count_copies(uint32_t n_plans) {

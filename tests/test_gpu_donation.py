@@ -1,0 +1,78 @@
+"""Donated work: launches whose whole work starts as one task.  The donated-task
+counter of the launch's own workspace shows that tasks were handed out, and the
+counts stay those of the oracle or of another plan of the same pattern."""
+import os
+import re
+
+import numpy as np
+import pytest
+
+import oracle
+import xmgen
+
+pytestmark = pytest.mark.gpu
+ONE_TASK = dict(split=4096, split_work=1 << 30)  # a root of up to 4,096 first-level candidates stays whole
+
+
+def constant(name):
+    """The value of a constant or control word in the launch interface's header."""
+    path = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2404_11105_amd", "csrc",
+                        "kernels.h")
+    text = re.search(name + r" = (?:(\d+)u << )?(\d+)[,;]", open(path).read())
+    return int(text.group(1)) << int(text.group(2)) if text.group(1) else int(text.group(2))
+
+
+@pytest.fixture(scope="module")
+def xa():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2404_11105_amd as xa
+    return xa
+
+
+def hub_of(g):
+    return np.array([int(np.argmax(g.out_deg() + g.in_deg()))], dtype=np.uint32)
+
+
+def run(xa, G, plan, roots, **opts):
+    """Counts, and how many tasks were donated (the queue's tail, in the control words
+    at the start of the workspace)."""
+    import torch
+    c = xa.Counter(G, [plan], roots=roots, **opts)
+    c.run()
+    counts, status = c.results()
+    assert status == [0]
+    return counts[0], int(c.workspace.view(torch.int32)[constant("kCtlDonTail")])
+
+
+def test_id_ranges_of_a_leaf_pass_are_handed_out(xa):
+    """One level below the root: only ranges of a leaf window can be donated."""
+    n = 4096
+    rng = np.random.default_rng(5)
+    u, v = np.nonzero(rng.random((n, n)) < 0.5)
+    g = xmgen.from_arcs(n, u, v)
+    G = xa.Graph(g, dense_rows=0)
+    p = xmgen.named("ffl")
+    plan = xa.Plan(p, reduced=False, graph=G, root_vertex=0)
+    assert plan.describe()["e"] == 2
+    root = np.array([7], dtype=np.uint32)
+    want = oracle.count(g, p, roots=root, root_vertex=0)
+    for opts in (dict(), dict(cap=8192), dict(waves_per_cu=4)):
+        got, donated = run(xa, G, plan, root, **ONE_TASK, **opts)
+        print("[case]", opts, "donated", donated, flush=True)
+        assert got == want and donated > 0
+
+
+def test_slots_are_handed_out_again(xa):
+    """More tasks than the queue has slots, and more than a launch had in all when
+    each slot was used once; counted by another plan too."""
+    g = xmgen.rmat(17, seed=1)
+    G = xa.Graph(g)
+    p = xmgen.named("c5chord")
+    root = hub_of(g)
+    want, _ = run(xa, G, xa.Plan(p, graph=G, root_vertex=0), root)
+    got, donated = run(xa, G, xa.Plan(p, reduced=False, graph=G, root_vertex=0), root)
+    print("[case] donated", donated, "slots", constant("kDonCap"), flush=True)
+    assert got == want
+    assert donated > constant("kDonCap") and donated > 1 << 18
