@@ -1339,11 +1339,9 @@ __device__ __forceinline__ void hold_rows(const Ctx& C, uint32_t nb, uint32_t& h
 }
 
 // Whether a task that has run for a while should look for waiting waves now.
-__device__ __forceinline__ bool time_to_look(Ctx& C) {
-    const uint32_t now = (uint32_t)__builtin_readcyclecounter();
-    if (now - C.looked < kDonateClocks) return false;
-    C.looked = now;
-    return true;
+__device__ __forceinline__ bool time_to_look(const Ctx& C, uint32_t& now) {
+    now = (uint32_t)__builtin_readcyclecounter();
+    return now - C.looked >= kDonateClocks;
 }
 
 // Work donation.  While some waves are idle (all queues drained), a wave that
@@ -1434,11 +1432,17 @@ __device__ __forceinline__ void donate_parents(Ctx& C, uint32_t start, uint32_t 
 // the partial matches [from, n) that are not counted yet, as id ranges below
 // their parents (level lv is expanded again there, for these ids only).
 // each: clocks a partial match took so far; a range should take kDonateWork.
-// Returns the new end of the window.
-__device__ __forceinline__ uint32_t donate_leaves(Ctx& C, uint32_t lv, uint32_t from, uint32_t n, uint32_t each) {
+// Returns the new end of the window.  A window with too little left to cut is
+// no look: the task's next one, between windows, may hand off parents.  (With
+// every look of a leaf pass counted, tasks of windows of 0.5 to 1 ms handed off
+// next to nothing: one task of R-MAT 15, 4-cycle unreduced 144 ms, TT4 + pendant
+// 429; now 75 and 44.)
+__device__ __forceinline__ uint32_t donate_leaves(Ctx& C, uint32_t lv, uint32_t from, uint32_t n, uint32_t now,
+                                                  uint32_t each) {
     if (n < from + 2 * kDonatePiece) return n;
     const uint64_t pieces = (uint64_t)each * ((n - from) / 2) / kDonateWork;
     if (pieces == 0) return n;
+    C.looked = now;
     uint32_t head, tail;
     uint32_t room = donation_room(C, head, tail);
     if (room == 0) return n;
@@ -1696,8 +1700,9 @@ __device__ __forceinline__ void count_leaves(Ctx& C, uint32_t lv, uint32_t npref
                 return;
             }
         }
-        if (lv > 0 && w0 > 0 && time_to_look(C))
-            nprefix = donate_leaves(C, lv, w0 + 64, nprefix, (C.looked - entered) / w0);
+        uint32_t now;
+        if (lv > 0 && w0 > 0 && time_to_look(C, now))
+            nprefix = donate_leaves(C, lv, w0 + 64, nprefix, now, (now - entered) / w0);
         const uint32_t p = w0 + lane;
         const bool pv = p < nprefix;
         // walk the chain once: bound nodes of levels 0..lv
@@ -1783,7 +1788,11 @@ __device__ __forceinline__ void explore(Ctx& C, uint32_t n0, uint32_t start) {
                 break;
             }
         }
-        if (lv >= 2 && time_to_look(C) && C.looked - C.begun >= kDonateParents) donate_parents(C, start, lv);
+        uint32_t now;
+        if (lv >= 2 && time_to_look(C, now)) {
+            C.looked = now;
+            if (now - C.begun >= kDonateParents) donate_parents(C, start, lv);
+        }
         uint32_t nout = expand(C, lv);
         if (lv == e - 1) {
             if (nout) count_leaves<NONLIN, ROOMY>(C, lv, nout);

@@ -64,6 +64,22 @@ def test_id_ranges_of_a_leaf_pass_are_handed_out(xa):
         assert got == want and donated > 0
 
 
+@pytest.mark.parametrize("name", ["c4", "bifan"])
+def test_parents_are_handed_out_between_short_leaf_windows(xa, name):
+    """Leaf windows too short to be cut (under two looks long) must not keep the task
+    from handing off parents: a few wide donations only would leave hundreds of
+    waves idle."""
+    g = xmgen.rmat(15, seed=2)
+    G = xa.Graph(g)
+    p = xmgen.named(name)
+    plan = xa.Plan(p, reduced=False, graph=G, root_vertex=0)
+    root = hub_of(g)
+    want, _ = run(xa, G, xa.Plan(p, graph=G, root_vertex=0), root)
+    got, donated = run(xa, G, plan, root, **ONE_TASK)
+    print("[case]", name, "donated", donated, flush=True)
+    assert got == want and donated > 1000
+
+
 def test_slots_are_handed_out_again(xa):
     """More tasks than the queue has slots, and more than a launch had in all when
     each slot was used once; counted by another plan too."""
