@@ -2196,11 +2196,15 @@ __global__ void init_kernel(InitArgs a) {
     }
 }
 
-// Per-plan totals, and status from the flags the count kernel raised.
+// Per-plan totals, and status from the flags the count kernel raised (one block).
 __global__ void finalize_kernel(KArgs a) {
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < a.n_plans; i += gridDim.x * blockDim.x) {
+    // every donated task must have been taken (the head may stop short of the
+    // last ones): one left behind would be missing from the counts
+    const bool left = __syncthreads_or(don_left(a.don, kDonWords, a.don_cap, a.ctl[kCtlDonHead], a.ctl[kCtlDonTail],
+                                                threadIdx.x, blockDim.x)) != 0;
+    for (uint32_t i = threadIdx.x; i < a.n_plans; i += blockDim.x) {
         int32_t st = 0;
-        if (a.ctl[kCtlBadPlan]) st = -1;
+        if (a.ctl[kCtlBadPlan] || (left && !a.ctl[kCtlCancelled])) st = -1;
         else if (a.ctl[kCtlQueueFull]) st = -6;
         else if (a.ctl[kCtlCancelled]) st = -7;
         else if (a.plan_flags[i] & 1u) st = -5;

@@ -30,4 +30,14 @@ XM_HD inline bool don_fits(uint32_t head, uint32_t tail, uint32_t k, uint32_t ca
     return tail <= kDonLast - k && tail + k - head <= cap;
 }
 
+// Whether a reserved task of [head, tail) was never read: slots' words at don,
+// `words` a slot, the ready word second; looks at every step-th task from `first` on.
+XM_HD inline bool don_left(const uint32_t* don, uint32_t words, uint32_t cap, uint32_t head, uint32_t tail,
+                           uint32_t first, uint32_t step) {
+    bool left = false;
+    for (uint64_t s = (uint64_t)head + first; s < tail; s += step)
+        left = left || don[(uint64_t)don_slot((uint32_t)s, cap) * words + 1] != don_read((uint32_t)s, cap);
+    return left;
+}
+
 }  // namespace xm

@@ -8,5 +8,8 @@ uint32_t t_slot(uint32_t s, uint32_t cap) { return xm::don_slot(s, cap); }
 uint32_t t_published(uint32_t s, uint32_t cap) { return xm::don_published(s, cap); }
 uint32_t t_read(uint32_t s, uint32_t cap) { return xm::don_read(s, cap); }
 int t_fits(uint32_t head, uint32_t tail, uint32_t k, uint32_t cap) { return xm::don_fits(head, tail, k, cap) ? 1 : 0; }
+int t_left(const uint32_t* don, uint32_t words, uint32_t cap, uint32_t head, uint32_t tail, uint32_t first, uint32_t step) {
+    return xm::don_left(don, words, cap, head, tail, first, step) ? 1 : 0;
+}
 uint32_t t_last() { return xm::kDonLast; }
 }

@@ -42,6 +42,28 @@ def test_ready_words_never_repeat_and_the_numbers_end(lib, cap):
     assert not lib.t_fits(last, last, 1, cap) and not lib.t_fits(last - 2, last - 2, 3, cap)
 
 
+@pytest.mark.parametrize("cap, head, tail", [(4, 0, 0), (4, 0, 3), (4, 6, 10), (2048, 4095, 4097), (2048, 5000, 6100)])
+def test_an_entry_left_behind_is_found(lib, cap, head, tail):
+    """The check at the end of a launch: 256 threads, each over its share of the
+    entries from the head on."""
+    W = 9
+    don = (ctypes.c_uint32 * (W * cap))()
+
+    def left():
+        return any(lib.t_left(don, W, cap, head, tail, t, 256) for t in range(256))
+
+    for s in range(tail):
+        don[W * lib.t_slot(s, cap) + 1] = lib.t_read(s, cap)
+    assert not left()
+    for s in sorted({head, (head + tail) // 2, tail - 1}):
+        if head <= s < tail:
+            for state in (0, 1, 2):  # reserved, published, claimed
+                don[W * lib.t_slot(s, cap) + 1] = lib.t_read(s, cap) - 3 + state
+                assert left()
+            don[W * lib.t_slot(s, cap) + 1] = lib.t_read(s, cap)
+    assert not left()
+
+
 class Model:
     """waves[i] starts with work[i] units; a wave with several units left hands
     some to the queue while waves wait, as many as wait beyond the queue."""
