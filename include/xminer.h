@@ -278,9 +278,10 @@ typedef struct xm_count_opts {
     uint32_t cap;           /* per-level candidate buffer entries (default 4096,
                                at least split) */
     uint32_t waves_per_cu;  /* resident waves per compute unit, 4..32 (default:
-                               24, or when LDS allows fewer, or no list of the
-                               graph has more than 64 elements, 12 or as many as
-                               LDS allows; at most 24 are launched).
+                               24, or when LDS allows fewer, or the graph has
+                               at most 131,072 nodes and no list of more than 64
+                               elements, 12 or as many as LDS allows; at most 24
+                               are launched).
                                Launches of at most 12 waves per CU run a build
                                of the count kernel that keeps all its state in
                                registers; larger ones a build limited to 80

@@ -200,11 +200,17 @@ int make_layout(const xm_graph_t* g, uint32_t n_plans, const xm_plan_t* const* p
         // that keeps everything in registers at its kRoomyBlocksPerCu blocks
         // (measured: 256 plans on R-MAT 22 1,340 ms at 3 blocks against
         // 1,374 ms at 4; TT4 + pendant on R-MAT 20 2,199 ms against 2,787 ms).
-        // So too on a graph without long lists: there the filter of shared
+        // So too on a small graph without long lists: there the filter of shared
         // lists, which only that kernel has, saves more than the waves hide
-        // (four motifs on 2,000 nodes 288 us at 8 blocks, 256 us at 3).
+        // (four motifs on 2,000 nodes 288 us at 8 blocks, 256 us at 3), as long
+        // as most of its hits are certain (up to two ids a bit).  At 3 and 6
+        // blocks, uniform graphs of degree 16 without hubs, four motifs and
+        // {4-cycle, TT4 + pendant, 5-cycle + chord}: 65,537 nodes 7.3 / 8.6 and
+        // 9.4 / 9.1 ms, 131,071 nodes 13.7 / 14.8 and 18.4 / 17.3, 200,003 nodes
+        // 20.8 / 20.3 and 28.0 / 24.9, 1,000,003 nodes 101 / 100 and 140 / 118.
         int bpc = xm::count_blocks_per_cu(L.nonlinear, (size_t)L.lds_words * 4 * xm::kWavesPerBlock);
-        if (bpc < xm::kFullBlocksPerCu || g->n_hubs == 0) bpc = std::min(bpc, xm::kRoomyBlocksPerCu);
+        if (bpc < xm::kFullBlocksPerCu || (g->n_hubs == 0 && g->n <= 2 * 32 * xm::kFilterMaxWords))
+            bpc = std::min(bpc, xm::kRoomyBlocksPerCu);
         L.waves_per_cu = (uint32_t)std::max(1, std::min(bpc, xm::kFullBlocksPerCu)) * xm::kWavesPerBlock;
     }
     const uint32_t blocks = (L.waves_per_cu + xm::kWavesPerBlock - 1) / xm::kWavesPerBlock;

@@ -1,0 +1,31 @@
+"""The default number of waves, read from the workspace it needs, and the counts
+of launches on each side of the rule."""
+import pytest
+
+import oracle
+import xmgen
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def xa():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2404_11105_amd as xa
+    return xa
+
+
+@pytest.mark.parametrize("n, waves", [(3001, 12), (131072, 12), (131073, 24), (300007, 24)])
+def test_graphs_without_long_lists(xa, n, waves):
+    """Few nodes: 12 waves per CU, whose kernel tests short lists against a bit map
+    in LDS; more nodes than twice the map's bits: 24."""
+    g = xmgen.uniform_digraph(n, 4 * n, 1)
+    pats = [xmgen.named("ffl"), xmgen.named("c4")]
+    G = xa.Graph(g)
+    plans = [xa.Plan(p, graph=G) for p in pats]
+    print("[case]", n, flush=True)
+    assert xa.api.workspace_bytes(G, plans) == xa.api.workspace_bytes(G, plans, waves_per_cu=waves)
+    assert xa.api.workspace_bytes(G, plans, waves_per_cu=12) != xa.api.workspace_bytes(G, plans, waves_per_cu=24)
+    assert xa.count(G, plans) == [oracle.count(g, p) for p in pats]
