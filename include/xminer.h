@@ -280,12 +280,14 @@ typedef struct xm_count_opts {
     uint32_t waves_per_cu;  /* resident waves per compute unit, 4..32 (default:
                                24, or when LDS allows fewer, or the graph has
                                at most 131,072 nodes and no list of more than 64
-                               elements, 12 or as many as LDS allows; at most 24
-                               are launched).
-                               Launches of at most 12 waves per CU run a build
-                               of the count kernel that keeps all its state in
-                               registers; larger ones a build limited to 80
-                               VGPRs that spills some of it. */
+                               elements, or the launch lists or merges, 12 or as
+                               many as LDS allows; at most 24 are launched, 12
+                               when listing or merging).
+                               Launches of at most 12 waves per CU (small ones
+                               start no more than they have work for) run a build
+                               of the count kernel with twice the registers and
+                               next to no spills; larger ones a build limited to
+                               80 VGPRs that spills some of its state. */
     /* root subset: device array of n_roots node ids (< n, distinct); when
        non-NULL only these nodes are tried as images of the plan's start
        vertex (xm_plan_root_vertex).  Counts are then exact partial sums.

@@ -29,3 +29,25 @@ def test_graphs_without_long_lists(xa, n, waves):
     assert xa.api.workspace_bytes(G, plans) == xa.api.workspace_bytes(G, plans, waves_per_cu=waves)
     assert xa.api.workspace_bytes(G, plans, waves_per_cu=12) != xa.api.workspace_bytes(G, plans, waves_per_cu=24)
     assert xa.count(G, plans) == [oracle.count(g, p) for p in pats]
+
+
+@pytest.mark.parametrize("waves", [0, 12, 24])
+def test_listing_and_merging_launches(xa, waves):
+    """They run the kernel of 12 waves per CU, whatever is asked for, and by default
+    no more are reserved.  Every embedding is listed, and counts are the oracle's."""
+    import torch
+    g = xmgen.rmat(11, seed=4)
+    p = xmgen.named("ffl")
+    want = oracle.count(g, p)
+    G = xa.Graph(g)
+    plan = xa.Plan(p, reduced=False, graph=G)
+    rows = torch.empty(3 * 16, dtype=torch.int32, device=G.device)
+    n = torch.zeros(1, dtype=torch.int64, device=G.device)
+    for opts in (dict(listing=(rows, 16, n)), dict(merge_min=64)):
+        used = xa.api.workspace_bytes(G, [plan], waves_per_cu=waves, **opts)
+        assert used == xa.api.workspace_bytes(G, [plan], waves_per_cu=waves or 12, **opts)
+    print("[case]", waves, flush=True)
+    found, listed = xa.list_embeddings(G, p, cap=want, waves_per_cu=waves)
+    assert found == want and len({tuple(r) for r in listed.tolist()}) == want
+    G = xa.Graph(g, dense_rows=0)
+    assert xa.count(G, [xa.Plan(p, reduced=False, graph=G)], merge_min=16, waves_per_cu=waves) == [want]
