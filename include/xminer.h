@@ -281,8 +281,8 @@ typedef struct xm_count_opts {
                                24, or when LDS allows fewer, or the graph has
                                at most 131,072 nodes and no list of more than 64
                                elements, or the launch lists or merges, 12 or as
-                               many as LDS allows; at most 24 are launched, 12
-                               when listing or merging).
+                               many as LDS allows; more than 24, or than 12 when
+                               listing or merging, count as that many).
                                Launches of at most 12 waves per CU (small ones
                                start no more than they have work for) run a build
                                of the count kernel with twice the registers and

@@ -208,13 +208,16 @@ int make_layout(const xm_graph_t* g, uint32_t n_plans, const xm_plan_t* const* p
         // {4-cycle, TT4 + pendant, 5-cycle + chord}: 65,537 nodes 7.3 / 8.6 and
         // 9.4 / 9.1 ms, 131,071 nodes 13.7 / 14.8 and 18.4 / 17.3, 200,003 nodes
         // 20.8 / 20.3 and 28.0 / 24.9, 1,000,003 nodes 101 / 100 and 140 / 118.
-        // Listing and merging are in that kernel only (merging triangles of R-MAT
-        // 15 with 6 blocks per CU started 2.02 ms, with 3 1.90).
+        // (Listing and merging are in that kernel only: merging triangles of R-MAT
+        // 15 with 6 blocks per CU started 2.02 ms, with 3 1.90.)
         int bpc = xm::count_blocks_per_cu(L.nonlinear, (size_t)L.lds_words * 4 * xm::kWavesPerBlock);
-        if (bpc < xm::kFullBlocksPerCu || listing || merging || (g->n_hubs == 0 && g->n <= 2 * 32 * xm::kFilterMaxWords))
+        if (bpc < xm::kFullBlocksPerCu || (g->n_hubs == 0 && g->n <= 2 * 32 * xm::kFilterMaxWords))
             bpc = std::min(bpc, xm::kRoomyBlocksPerCu);
-        L.waves_per_cu = (uint32_t)std::max(1, std::min(bpc, xm::kFullBlocksPerCu)) * xm::kWavesPerBlock;
+        L.waves_per_cu = (uint32_t)std::max(1, bpc) * xm::kWavesPerBlock;
     }
+    // no more than the kernel's registers let be resident at once
+    L.waves_per_cu = std::min<uint32_t>(
+        L.waves_per_cu, (listing || merging ? xm::kRoomyBlocksPerCu : xm::kFullBlocksPerCu) * xm::kWavesPerBlock);
     const uint32_t blocks = (L.waves_per_cu + xm::kWavesPerBlock - 1) / xm::kWavesPerBlock;
     if (!merging && !listing && blocks <= (uint32_t)xm::kRoomyBlocksPerCu) {
         // the largest bit map that the resident blocks' LDS leaves room for, at
@@ -320,11 +323,7 @@ int make_layout(const xm_graph_t* g, uint32_t n_plans, const xm_plan_t* const* p
         // starts no more blocks than its items and those waiters need
         const uint64_t n_src = (o && o->roots_dev) ? o->n_roots : g->n;
         const uint64_t tasks = (n_src + L.chunk - 1) / L.chunk * n_plans + items + xm::kMaxWaiters;
-        // (and no more than the kernel's registers let be resident at once)
-        const int per_cu = listing || merging ? xm::kRoomyBlocksPerCu : xm::kFullBlocksPerCu;
-        L.launch_blocks = (uint32_t)std::min<uint64_t>(
-            std::min<uint64_t>(L.n_blocks, (uint64_t)g->n_cu * per_cu),
-            (tasks + xm::kWavesPerBlock - 1) / xm::kWavesPerBlock);
+        L.launch_blocks = (uint32_t)std::min<uint64_t>(L.n_blocks, (tasks + xm::kWavesPerBlock - 1) / xm::kWavesPerBlock);
     }
     L.qbase[0] = 0;
     for (uint32_t q = 0; q < xm::kQueues; q++) L.qbase[q + 1] = L.qbase[q] + (uint32_t)qc[q];

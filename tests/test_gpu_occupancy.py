@@ -51,3 +51,24 @@ def test_listing_and_merging_launches(xa, waves):
     assert found == want and len({tuple(r) for r in listed.tolist()}) == want
     G = xa.Graph(g, dense_rows=0)
     assert xa.count(G, [xa.Plan(p, reduced=False, graph=G)], merge_min=16, waves_per_cu=waves) == [want]
+
+
+def test_more_waves_than_can_be_resident(xa):
+    """Asked for more waves than the kernel's registers allow: nothing is reserved
+    for the rest, and the autotuner does not try them."""
+    import torch
+    from paper_2404_11105_amd import tune
+    g = xmgen.rmat(11, seed=4)
+    p = xmgen.named("ffl")
+    G = xa.Graph(g)
+    plan = xa.Plan(p, reduced=False, graph=G)
+    size = xa.api.workspace_bytes
+    assert size(G, [plan], waves_per_cu=32) == size(G, [plan], waves_per_cu=24)
+    rows = torch.empty(3 * 16, dtype=torch.int32, device=G.device)
+    n = torch.zeros(1, dtype=torch.int64, device=G.device)
+    for opts in (dict(listing=(rows, 16, n)), dict(merge_min=64)):
+        assert size(G, [plan], waves_per_cu=24, **opts) == size(G, [plan], waves_per_cu=12, **opts)
+    assert max(dict(tune.SPACE)["waves_per_cu"]) == 24
+    want = oracle.count(g, p)
+    for waves in (24, 32):
+        assert xa.count(G, [plan], waves_per_cu=waves) == [want]
