@@ -268,7 +268,9 @@ typedef struct xm_count_opts {
     uint32_t flags;         /* reserved, must be 0 */
     uint32_t chunk;         /* roots taken per work grab (<= 64; default 0: about
                                64 root tasks per resident wave, i.e.
-                               ceil(roots x plans / (waves x 64)) clamped to 1..64) */
+                               ceil(roots x plans / (waves x 64)) clamped to
+                               1..64; as for 12 waves per CU where no list has
+                               more than 64 elements and waves_per_cu is 0) */
     uint32_t split;         /* a root whose first-level candidate list has L1
                                entries is split into stealable sub-ranges of
                                min(split, split_work / L1) entries (at least 1)
@@ -278,10 +280,11 @@ typedef struct xm_count_opts {
     uint32_t cap;           /* per-level candidate buffer entries (default 4096,
                                at least split) */
     uint32_t waves_per_cu;  /* resident waves per compute unit, 4..32 (default:
-                               24, or when LDS allows fewer, or the graph has
-                               at most 131,072 nodes and no list of more than 64
-                               elements, or the launch lists or merges, 12 or as
-                               many as LDS allows; more than 24, or than 12 when
+                               24, or when LDS allows fewer, or no list of the
+                               graph has more than 64 elements and the plans
+                               have little to do (m^2 / n below 2^28, or at most
+                               one level below the root), or the launch lists or
+                               merges, 12 or as many as LDS allows; more than 24, or than 12 when
                                listing or merging, count as that many).
                                Launches of at most 12 waves per CU (small ones
                                start no more than they have work for) run a build

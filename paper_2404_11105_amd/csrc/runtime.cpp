@@ -112,6 +112,9 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 constexpr uint64_t kMaxQueueBytes = 2ull << 30;  // split task queue, at most
 constexpr uint64_t kMaxRootItems = 0xFFFFFFFFull - 64;  // root items per launch (32-bit item ids)
 
+// 2-paths below which a graph without long lists gets 12 waves per CU
+constexpr double kFewPaths = 1u << 28;
+
 // Defaults of launches on the static scratch array (xm_count_static): fewer
 // resident waves and smaller level windows, so that the workspace of most
 // launches fits the array.
@@ -200,19 +203,25 @@ int make_layout(const xm_graph_t* g, uint32_t n_plans, const xm_plan_t* const* p
         // that keeps everything in registers at its kRoomyBlocksPerCu blocks
         // (measured: 256 plans on R-MAT 22 1,340 ms at 3 blocks against
         // 1,374 ms at 4; TT4 + pendant on R-MAT 20 2,199 ms against 2,787 ms).
-        // So too on a small graph without long lists: there the filter of shared
-        // lists, which only that kernel has, saves more than the waves hide
-        // (four motifs on 2,000 nodes 288 us at 8 blocks, 256 us at 3), as long
-        // as most of its hits are certain (up to two ids a bit).  At 3 and 6
-        // blocks, uniform graphs of degree 16 without hubs, four motifs and
-        // {4-cycle, TT4 + pendant, 5-cycle + chord}: 65,537 nodes 7.3 / 8.6 and
-        // 9.4 / 9.1 ms, 131,071 nodes 13.7 / 14.8 and 18.4 / 17.3, 200,003 nodes
-        // 20.8 / 20.3 and 28.0 / 24.9, 1,000,003 nodes 101 / 100 and 140 / 118.
+        // So too on graphs without long lists: there the filter of shared lists,
+        // which only that kernel has, and fewer waves to start save more than the
+        // waves hide (four motifs on 2,000 nodes 288 us at 8 blocks, 256 us at 3),
+        // except where plans of several enumerated levels have much to do: then
+        // several ids share a bit, every hit is verified, and the loads' latency
+        // decides.  The measure is the number of 2-paths from the roots, m^2 / n
+        // for all roots.  At 3 and 6 blocks, in ms, {feed-forward, 3-cycle, TT4 +
+        // out-pendant} / 5-cycle + chord / four motifs: 1.0e8 2-paths (1,000,003
+        // nodes of degree 10) 4.9 and 5.3 / 30.9 and 26.5 / 41.7 and 41.3; 2.8e8
+        // (1,100,009, 16) 9.7 and 8.8 / 103 and 94 / 111 and 110; 4.0e8 (4,000,037,
+        // 10) 16.7 and 16.2 / 128 and 108 / 163 and 163; 1.0e9 (4,000,037, 16) 36.8
+        // and 32.1 / 400 and 359 / 434 and 381.  Feed-forward triangles alone: 5.1
+        // and 5.3 at 2.8e8, 13.1 and 13.4 at 1.0e9.
         // (Listing and merging are in that kernel only: merging triangles of R-MAT
         // 15 with 6 blocks per CU started 2.02 ms, with 3 1.90.)
         int bpc = xm::count_blocks_per_cu(L.nonlinear, (size_t)L.lds_words * 4 * xm::kWavesPerBlock);
-        if (bpc < xm::kFullBlocksPerCu || (g->n_hubs == 0 && g->n <= 2 * 32 * xm::kFilterMaxWords))
-            bpc = std::min(bpc, xm::kRoomyBlocksPerCu);
+        const double n_src = (o && o->roots_dev) ? o->n_roots : g->n;
+        const bool light = L.e_max < 3 || (double)g->m / g->n * ((double)g->m / g->n) * n_src < kFewPaths;
+        if (bpc < xm::kFullBlocksPerCu || (g->n_hubs == 0 && light)) bpc = std::min(bpc, xm::kRoomyBlocksPerCu);
         L.waves_per_cu = (uint32_t)std::max(1, bpc) * xm::kWavesPerBlock;
     }
     // no more than the kernel's registers let be resident at once
@@ -236,9 +245,16 @@ int make_layout(const xm_graph_t* g, uint32_t n_plans, const xm_plan_t* const* p
     if (L.chunk == 0) {
         // about 64 root tasks per wave: one root per task on small batches,
         // up to 64 roots per task when plans x roots is large (each task has a
-        // fixed cost: a queue grab, the root filter, a flush)
+        // fixed cost: a queue grab, the root filter, a flush).  By default a
+        // graph without long lists gets the tasks of 12 waves per CU also where
+        // it runs 24: its tasks are even, and the queues hand out ~70 a us
+        // however many waves ask (out-star and 3-cycle, 300,007 nodes of degree
+        // 10: 4.34 ms with twice the tasks, 2.23 with these).
         const uint64_t n_src = (o && o->roots_dev) ? o->n_roots : g->n;
-        const uint64_t per = (uint64_t)L.n_waves * 64;
+        const bool given = (o && o->waves_per_cu) || on_static;
+        const uint32_t roomy = xm::kRoomyBlocksPerCu * xm::kWavesPerBlock;
+        const uint32_t w = !given && g->n_hubs == 0 ? std::min(L.waves_per_cu, roomy) : L.waves_per_cu;
+        const uint64_t per = (uint64_t)g->n_cu * w * 64;
         L.chunk = (uint32_t)std::min<uint64_t>(64, std::max<uint64_t>(1, (n_src * n_plans + per - 1) / per));
     }
     {
