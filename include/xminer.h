@@ -283,8 +283,9 @@ typedef struct xm_count_opts {
                                24, or when LDS allows fewer, or no list of the
                                graph has more than 64 elements and the plans
                                have little to do (m^2 / n below 2^28, or at most
-                               one level below the root), or the launch lists or
-                               merges, 12 or as many as LDS allows; more than 24, or than 12 when
+                               one level below the root), or no plan has a level
+                               below the root, or the launch lists or merges, 12
+                               or as many as LDS allows; more than 24, or than 12 when
                                listing or merging, count as that many).
                                Launches of at most 12 waves per CU (small ones
                                start no more than they have work for) run a build

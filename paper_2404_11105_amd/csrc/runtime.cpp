@@ -216,12 +216,17 @@ int make_layout(const xm_graph_t* g, uint32_t n_plans, const xm_plan_t* const* p
         // 10) 16.7 and 16.2 / 128 and 108 / 163 and 163; 1.0e9 (4,000,037, 16) 36.8
         // and 32.1 / 400 and 359 / 434 and 381.  Feed-forward triangles alone: 5.1
         // and 5.3 at 2.8e8, 13.1 and 13.4 at 1.0e9.
+        // And so where no plan has a level below the root: a root is then a few
+        // loads, and the cost of starting a wave decides (3-path 5,003 nodes of
+        // degree 100 0.41 ms at 3 blocks, 0.62 at 6; R-MAT 16 0.85 / 0.90, R-MAT 20
+        // 2.69 / 4.94, R-MAT 22 3.25 / 6.20; out-star of 5 on R-MAT 17 1.10 / 1.03).
         // (Listing and merging are in that kernel only: merging triangles of R-MAT
         // 15 with 6 blocks per CU started 2.02 ms, with 3 1.90.)
         int bpc = xm::count_blocks_per_cu(L.nonlinear, (size_t)L.lds_words * 4 * xm::kWavesPerBlock);
         const double n_src = (o && o->roots_dev) ? o->n_roots : g->n;
         const bool light = L.e_max < 3 || (double)g->m / g->n * ((double)g->m / g->n) * n_src < kFewPaths;
-        if (bpc < xm::kFullBlocksPerCu || (g->n_hubs == 0 && light)) bpc = std::min(bpc, xm::kRoomyBlocksPerCu);
+        if (bpc < xm::kFullBlocksPerCu || L.e_max == 1 || (g->n_hubs == 0 && light))
+            bpc = std::min(bpc, xm::kRoomyBlocksPerCu);
         L.waves_per_cu = (uint32_t)std::max(1, bpc) * xm::kWavesPerBlock;
     }
     // no more than the kernel's registers let be resident at once

@@ -37,6 +37,21 @@ def test_graphs_without_long_lists(xa, n, deg, names, waves):
     assert got == xa.count(G, plans, waves_per_cu=12) == xa.count(G, plans, waves_per_cu=24, chunk=1)
 
 
+@pytest.mark.parametrize("names, waves", [("path3", 12), ("arc,outstar3,mixed_star", 12), ("path3,ffl", 24)])
+def test_plans_without_levels_below_the_root(xa, names, waves):
+    g = xmgen.rmat(12, seed=5)
+    pats = [xmgen.named(p) for p in names.split(",")]
+    G = xa.Graph(g)
+    plans = [xa.Plan(p, graph=G) for p in pats]
+    print("[case]", names, flush=True)
+    assert xa.api.workspace_bytes(G, plans) == xa.api.workspace_bytes(G, plans, waves_per_cu=waves)
+    assert xa.api.workspace_bytes(G, plans, waves_per_cu=12) != xa.api.workspace_bytes(G, plans, waves_per_cu=24)
+    want = [oracle.count(g, p) if p.k < 4 else None for p in pats]
+    got = xa.count(G, plans)
+    assert all(w is None or w == c for w, c in zip(want, got))
+    assert got == xa.count(G, plans, waves_per_cu=24) == xa.count(G, plans, waves_per_cu=4)
+
+
 @pytest.mark.parametrize("waves", [0, 12, 24])
 def test_listing_and_merging_launches(xa, waves):
     """They run the kernel of 12 waves per CU, whatever is asked for, and by default
