@@ -39,7 +39,6 @@ static_assert(sizeof(PlanDesc) % 4 == 0, "plan descriptors are copied in 32-bit 
 
 constexpr uint32_t kSkip = 0xFFFFFFFFu;
 constexpr uint32_t kIdlePolls = 1u << 13;  // polls a waiting wave makes for donated work
-constexpr uint32_t kIdleTurns = 1u << 10;  // times a wave waits on because work was donated as it left
 constexpr uint32_t kNapMax = 128;          // longest pause between two polls, in sleeps of 512 clocks (~27 us)
 // Work donation: clocks a task runs before it looks whether other waves wait,
 // and between such looks (~0.4 ms); partial matches of one parent in a donated
@@ -263,6 +262,7 @@ struct Ctx {
     uint32_t lane;
     unsigned long long acc_lo, acc_hi;  // per-lane 128-bit partial (leaf groups)
     bool ovf;                           // this lane's partial or a leaf-group term left the 128-bit range
+    uint32_t given;                     // sequence number after this wave's last donated task (0: none)
     bool stop;                          // the cancel flag was seen: leave the task
     uint32_t polls;                     // leaf blocks since the last look at the cancel flag
     uint32_t begun, looked;             // clock of the task's start, and of its last look for waiting waves
@@ -1380,7 +1380,9 @@ __device__ __forceinline__ uint32_t reserve_slots(Ctx& C, uint32_t k, uint32_t h
     uint32_t base = kSkip;
     if (C.lane == 0 && don_fits(head, tail, k, a.don_cap) && atomicCAS(&a.ctl[kCtlDonTail], tail, tail + k) == tail)
         base = tail;
-    return uni(__shfl(base, 0, 64));
+    base = uni(__shfl(base, 0, 64));
+    if (base != kSkip) C.given = base + k;
+    return base;
 }
 // One donated task: level l below entry idx of level l-1, ids in [xlo, xhi).
 __device__ __forceinline__ void donate(Ctx& C, uint32_t seq, uint32_t l, uint32_t idx, uint32_t xlo, uint32_t xhi) {
@@ -1832,6 +1834,7 @@ __global__ void __launch_bounds__(kBlockThreads, MINB) count_kernel(KArgs a) {
     C.ovf = false;
     C.pi = 0;
     C.P = a.plans;
+    C.given = 0;
     C.stop = false;
     C.polls = 0;
     C.begun = C.looked = 0;
@@ -1948,19 +1951,18 @@ __global__ void __launch_bounds__(kBlockThreads, MINB) count_kernel(KArgs a) {
             // task.  About kMaxWaiters waves wait (the others leave at once),
             // and they poll with growing pauses, so waiting waves do not crowd
             // the cache lines the working waves update.
-            // No entry is left behind: a wave that donated leaves only after it
-            // has read a nonzero number of waiters, and a waiter looks at the
-            // queue once more after it has taken itself off that number, so of
-            // the two the later one sees the entry.  (With donors that stayed until
-            // the queue was empty, thousands of them polled it: three unreduced
-            // plans on a hub root of R-MAT 15 322 ms, now 43.)
+            // No entry is left behind: a wave that donated leaves only when the
+            // head has passed its last entry, whatever the number of waiters.
+            // (With donors that stayed until the queue was empty, thousands of
+            // them polled it: three unreduced plans on a hub root of R-MAT 15 322
+            // ms, now 43.)
             uint32_t idle = 0;
             if (ln == 0) idle = __atomic_load_n(&a.ctl[kCtlIdle], __ATOMIC_RELAXED);
-            // (between the read and the add a few more waves than kMaxWaiters
-            // may come in; they may wait as well)
-            bool wait = uni(__shfl(idle, 0, 64)) < kMaxWaiters;
-            for (uint32_t turn = 0; wait && turn < kIdleTurns; turn++) {
-                if (ln == 0) atomicAdd(&a.ctl[kCtlIdle], 1u);
+            const bool wait = uni(__shfl(idle, 0, 64)) < kMaxWaiters;
+            if (wait || C.given) {
+                // between the read and this add a few more waves than
+                // kMaxWaiters may come in; they may wait as well
+                if (wait && ln == 0) atomicAdd(&a.ctl[kCtlIdle], 1u);
                 uint32_t nap = 1;
                 for (uint32_t polls = 0; polls < kIdlePolls; polls++) {
                     // queue entries [head, tail).  A waiter tries an entry of its own
@@ -1995,6 +1997,7 @@ __global__ void __launch_bounds__(kBlockThreads, MINB) count_kernel(KArgs a) {
                         item = got;
                         break;
                     }
+                    if (!wait && h >= C.given) break;
                     // a line of control words serves ~70 accesses a us: hundreds of
                     // waiters that look at once slow every other update down
                     if (h >= t) {
@@ -2013,17 +2016,7 @@ __global__ void __launch_bounds__(kBlockThreads, MINB) count_kernel(KArgs a) {
                     for (uint32_t z = 0; z < nap; z++) __builtin_amdgcn_s_sleep(8);
                     nap = nap < kNapMax ? nap * 2 : kNapMax;
                 }
-                // (the count has arrived before the queue is read again)
-                uint32_t more = 0;
-                if (ln == 0) {
-                    const uint32_t was = atomicSub(&a.ctl[kCtlIdle], 1u);
-                    asm volatile("" : : "v"(was) : "memory");
-                    if (kind == 2) {
-                        const uint32_t h = __atomic_load_n(&a.ctl[kCtlDonHead], __ATOMIC_RELAXED);
-                        more = h < __atomic_load_n(&a.ctl[kCtlDonTail], __ATOMIC_RELAXED);
-                    }
-                }
-                wait = uni(__shfl(more, 0, 64)) != 0;
+                if (wait && ln == 0) atomicSub(&a.ctl[kCtlIdle], 1u);
             }
         }
         if (kind == 3) {

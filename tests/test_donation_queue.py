@@ -81,6 +81,7 @@ class Model:
     def wave(self, me, units):
         L, cap = self.lib, self.cap
         self.active += 1
+        given = 0  # the sequence number after this wave's last donated task
         while True:
             # ---- work, donating between units
             while units:
@@ -101,7 +102,7 @@ class Model:
                 k = min(units // 2, room, cap)
                 if k <= 0 or not L.t_fits(head, tail, k, cap) or self.tail != tail:
                     continue
-                self.tail = tail + k  # (the compare-and-swap above)
+                self.tail = given = tail + k  # (the compare-and-swap above)
                 yield
                 share = units // (2 * k)
                 for s in range(tail, tail + k):
@@ -117,9 +118,10 @@ class Model:
             wait = self.idle < self.max_waiters
             yield
             got = None
-            while wait:
-                self.idle += 1
-                yield
+            if wait or given:
+                if wait:
+                    self.idle += 1
+                    yield
                 for poll in range(10 ** 6):
                     h = self.head
                     yield
@@ -147,19 +149,16 @@ class Model:
                             i += 1
                         if got is not None:
                             break
-                    else:
+                    if not wait and h >= given:
+                        break
+                    if h >= t:
                         act = self.active
                         yield
                         if act == 0:
                             break
-                self.idle -= 1
-                yield
-                if got is not None:
-                    break
-                h = self.head
-                yield
-                wait = h < self.tail
-                yield
+                if wait:
+                    self.idle -= 1
+                    yield
             if got is None:
                 return
             self.active += 1
