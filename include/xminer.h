@@ -290,8 +290,8 @@ typedef struct xm_count_opts {
                                Launches of at most 12 waves per CU (small ones
                                start no more than they have work for) run a build
                                of the count kernel with twice the registers and
-                               next to no spills; larger ones a build limited to
-                               80 VGPRs that spills some of its state. */
+                               no scratch; larger ones a build limited to 80
+                               VGPRs that spills some of its state. */
     /* root subset: device array of n_roots node ids (< n, distinct); when
        non-NULL only these nodes are tried as images of the plan's start
        vertex (xm_plan_root_vertex).  Counts are then exact partial sums.

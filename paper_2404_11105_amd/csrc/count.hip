@@ -213,7 +213,8 @@ struct Lds {
     uint32_t* hist;      // [signature masks][64]
     uint32_t* filt;      // [filt_words]: bit map of a shared list, or embeddings to be listed
     uint32_t* st;        // wave state: cur[8], pofs[8], n[8], a donated id range: level, from, to;
-                         // the filter's list: address (2 words), length
+                         // the filter's list: address (2 words), length; sequence
+                         // number after the wave's last donated task
     uint32_t* mbuf;      // [kMergeChunk]: probe-list chunk of the cooperative merge
 };
 
@@ -262,7 +263,6 @@ struct Ctx {
     uint32_t lane;
     unsigned long long acc_lo, acc_hi;  // per-lane 128-bit partial (leaf groups)
     bool ovf;                           // this lane's partial or a leaf-group term left the 128-bit range
-    uint32_t given;                     // sequence number after this wave's last donated task (0: none)
     bool stop;                          // the cancel flag was seen: leave the task
     uint32_t polls;                     // leaf blocks since the last look at the cancel flag
     uint32_t begun, looked;             // clock of the task's start, and of its last look for waiting waves
@@ -1381,7 +1381,7 @@ __device__ __forceinline__ uint32_t reserve_slots(Ctx& C, uint32_t k, uint32_t h
     if (C.lane == 0 && don_fits(head, tail, k, a.don_cap) && atomicCAS(&a.ctl[kCtlDonTail], tail, tail + k) == tail)
         base = tail;
     base = uni(__shfl(base, 0, 64));
-    if (base != kSkip) C.given = base + k;
+    if (base != kSkip && C.lane == 0) C.s.st[30] = base + k;
     return base;
 }
 // One donated task: level l below entry idx of level l-1, ids in [xlo, xhi).
@@ -1811,9 +1811,9 @@ __device__ __forceinline__ void explore(Ctx& C, uint32_t n0, uint32_t start) {
 }
 
 // Two register budgets.  MINB resident blocks per CU: kFullBlocksPerCu (6 waves
-// per SIMD, 80 VGPRs, some state spilled to scratch) for launches of more than
-// kRoomyBlocksPerCu blocks per CU, and kRoomyBlocksPerCu (3 waves per SIMD, the
-// whole kernel in registers) for launches of at most that many.  The larger one
+// per SIMD, 80 VGPRs, 90 of them spilled, 230-280 B of scratch a lane) for launches of more than
+// kRoomyBlocksPerCu blocks per CU, and kRoomyBlocksPerCu (3 waves per SIMD, no
+// scratch) for launches of at most that many.  The larger one
 // at 8 / 7 / 6 blocks: four motifs on R-MAT 16 18.2 / 18.5 / 17.8 ms, unreduced
 // 152 / 152 / 144 ms, a tenth of the roots 38.6 / 38.6 / 37.6 ms.
 template <bool NONLIN, int MINB>
@@ -1824,7 +1824,8 @@ __global__ void __launch_bounds__(kBlockThreads, MINB) count_kernel(KArgs a) {
     C.a = &a;
     C.lane = lane_id();
     // uniform over the wave, stated so: what is addressed from it stays in scalar
-    // registers (roomy kernels 168 -> 142 and 161 -> 133 VGPRs)
+    // registers (without it the roomy kernels spill 15 and 18 of their 168 VGPRs,
+    // with it none of 168 and 162)
     const uint32_t wid = uni(threadIdx.x >> 6);
     C.s = carve(smem + wid * a.lds_words, a.lds_rows, a.maxc, a.merge_min != 0xFFFFFFFFu,
                 a.filt_words);
@@ -1834,7 +1835,6 @@ __global__ void __launch_bounds__(kBlockThreads, MINB) count_kernel(KArgs a) {
     C.ovf = false;
     C.pi = 0;
     C.P = a.plans;
-    C.given = 0;
     C.stop = false;
     C.polls = 0;
     C.begun = C.looked = 0;
@@ -1845,7 +1845,7 @@ __global__ void __launch_bounds__(kBlockThreads, MINB) count_kernel(KArgs a) {
     // 64-bit: the host keeps the product below 2^32 (root items are 32-bit)
     const uint64_t chunks_per_plan = ((uint64_t)a.n_src + a.chunk - 1) / a.chunk;
     const uint64_t total_chunks = chunks_per_plan * a.n_plans;
-    if (C.lane < 3) C.s.st[27 + C.lane] = 0;  // no list is in the filter yet
+    if (C.lane < 4) C.s.st[27 + C.lane] = 0;  // no list is in the filter yet, nothing was donated
     Lvl F0 = lvl_arrays(C.scr, a.cap, 0);
     uint32_t taken = 0;
     // root items (item = chunk index x n_plans + plan) come from kQueues
@@ -1959,7 +1959,8 @@ __global__ void __launch_bounds__(kBlockThreads, MINB) count_kernel(KArgs a) {
             uint32_t idle = 0;
             if (ln == 0) idle = __atomic_load_n(&a.ctl[kCtlIdle], __ATOMIC_RELAXED);
             const bool wait = uni(__shfl(idle, 0, 64)) < kMaxWaiters;
-            if (wait || C.given) {
+            const uint32_t given = uni(C.s.st[30]);
+            if (wait || given) {
                 // between the read and this add a few more waves than
                 // kMaxWaiters may come in; they may wait as well
                 if (wait && ln == 0) atomicAdd(&a.ctl[kCtlIdle], 1u);
@@ -1997,7 +1998,7 @@ __global__ void __launch_bounds__(kBlockThreads, MINB) count_kernel(KArgs a) {
                         item = got;
                         break;
                     }
-                    if (!wait && h >= C.given) break;
+                    if (!wait && h >= given) break;
                     // a line of control words serves ~70 accesses a us: hundreds of
                     // waiters that look at once slow every other update down
                     if (h >= t) {
