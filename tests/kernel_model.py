@@ -6,10 +6,11 @@ fallback, leaf-group counting: single-signature passes and per-mask
 intersection sizes) on numpy arrays, one simulated wave at a time, so that
 termination, cursor arithmetic and buffer bounds can be checked on the CPU
 for any tuning.  It asserts every buffer index it uses.  It runs the tasks in
-order on one wave: the XCD-local split queues, work donation between waves
-and the dense-row representation of probe lists change which wave does a
-task and how a membership is tested, not what a task computes, and are not
-modelled.
+order on one wave.  The XCD-local split queues and the dense-row
+representation of probe lists change which wave does a task and how a
+membership is tested, not what a task computes, and are not modelled.  Nor is
+work donation, which cuts a task: a donated id range expands a part of its
+parent's base list and completes no child segment.
 """
 from __future__ import annotations
 
