@@ -92,3 +92,36 @@ def test_slots_are_handed_out_again(xa):
     print("[case] donated", donated, "slots", constant("kDonCap"), flush=True)
     assert got == want
     assert donated > constant("kDonCap") and donated > 1 << 18
+
+
+def test_donated_ranges_list_every_embedding_once(xa):
+    n = 2048
+    rng = np.random.default_rng(6)
+    u, v = np.nonzero(rng.random((n, n)) < 0.5)
+    g = xmgen.from_arcs(n, u, v)
+    G = xa.Graph(g, dense_rows=0)
+    p = xmgen.named("ffl")
+    plan = xa.Plan(p, reduced=False, graph=G, root_vertex=0)
+    root = np.array([7], dtype=np.uint32)
+    want = oracle.count(g, p, roots=root, root_vertex=0)
+    got, donated = run(xa, G, plan, root, **ONE_TASK, list_cap=want)
+    print("[case] listing, donated", donated, flush=True)
+    c = xa.Counter(G, [plan], roots=root, list_cap=want, **ONE_TASK)
+    c.run()
+    found, rows = c.listed()
+    rows = rows.astype(np.int64)
+    assert got == found == want and donated > 0
+    assert (rows[:, 0] == 7).all() and np.unique(rows[:, 1] * n + rows[:, 2]).size == want
+
+
+def test_donation_on_the_static_array(xa):
+    from tests.test_zz_no_alloc import static_count
+    g = xmgen.rmat(15, seed=2)
+    G = xa.Graph(g)
+    c = xa.Counter(G, [xa.Plan(xmgen.named("c5chord"), graph=G, root_vertex=0)], roots=hub_of(g))
+    c.run()
+    want = c.results()[0]
+    plan = xa.Plan(xmgen.named("c5chord"), reduced=False, graph=G, root_vertex=0)
+    for _ in range(2):
+        got, status = static_count(xa, G, [plan], roots=c.roots, roots_host=c.roots_host)
+        assert status == [0] and got == want
