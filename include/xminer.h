@@ -282,7 +282,8 @@ typedef struct xm_count_opts {
     uint32_t waves_per_cu;  /* resident waves per compute unit, 4..32 (default:
                                24, or when LDS allows fewer, or no list of the
                                graph has more than 64 elements and the plans
-                               have little to do (m^2 / n below 2^28, or at most
+                               have little to do (m^2 / n, less for a subset or
+                               share of the roots, below 2^28, or at most
                                one level below the root), or no plan has a level
                                below the root, or the launch lists or merges, 12
                                or as many as LDS allows; more than 24, or than 12 when

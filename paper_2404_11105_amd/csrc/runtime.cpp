@@ -5,6 +5,7 @@
 #include <algorithm>
 #include <cstddef>
 #include <atomic>
+#include <cmath>
 #include <functional>
 #include <cstdio>
 #include <cstring>
@@ -162,6 +163,7 @@ int make_layout(const xm_graph_t* g, uint32_t n_plans, const xm_plan_t* const* p
     L.nonlinear = false;
     uint32_t masks = 0;  // signature masks of the plan with the most (a power of two)
     uint32_t splittable = 0;
+    uint32_t deep_share = 64;  // smallest root share exponent of a plan with two levels below the root (64: none)
     for (uint32_t i = 0; i < n_plans; i++) {
         if (!plans[i]) return fail(XM_ERR_INVALID, "plan is NULL");
         const PlanDesc& D = plans[i]->desc;
@@ -175,6 +177,7 @@ int make_layout(const xm_graph_t* g, uint32_t n_plans, const xm_plan_t* const* p
             masks = std::max(masks, 1u << D.n_sig);
         }
         if (D.e >= 2) splittable++;
+        if (D.e >= 3) deep_share = std::min<uint32_t>(deep_share, D.root_share);
         // a symmetry-broken plan counts one embedding per orbit: neither the
         // embeddings of a root subset nor a listing can be read from it
         if (!g->new_of_old.empty() && o && o->roots_dev)
@@ -208,8 +211,8 @@ int make_layout(const xm_graph_t* g, uint32_t n_plans, const xm_plan_t* const* p
         // waves hide (four motifs on 2,000 nodes 288 us at 8 blocks, 256 us at 3),
         // except where plans of several enumerated levels have much to do: then
         // several ids share a bit, every hit is verified, and the loads' latency
-        // decides.  The measure is the number of 2-paths from the roots, m^2 / n
-        // for all roots.  At 3 and 6 blocks, in ms, {feed-forward, 3-cycle, TT4 +
+        // decides.  The measure is the number of 2-paths from those plans' roots,
+        // m^2 / n for all roots (less for a root subset or share).  At 3 and 6 blocks, in ms, {feed-forward, 3-cycle, TT4 +
         // out-pendant} / 5-cycle + chord / four motifs: 1.0e8 2-paths (1,000,003
         // nodes of degree 10) 4.9 and 5.3 / 30.9 and 26.5 / 41.7 and 41.3; 2.8e8
         // (1,100,009, 16) 9.7 and 8.8 / 103 and 94 / 111 and 110; 4.0e8 (4,000,037,
@@ -224,7 +227,8 @@ int make_layout(const xm_graph_t* g, uint32_t n_plans, const xm_plan_t* const* p
         // 15 with 6 blocks per CU started 2.02 ms, with 3 1.90.)
         int bpc = xm::count_blocks_per_cu(L.nonlinear, (size_t)L.lds_words * 4 * xm::kWavesPerBlock);
         const double n_src = (o && o->roots_dev) ? o->n_roots : g->n;
-        const bool light = L.e_max < 3 || (double)g->m / g->n * ((double)g->m / g->n) * n_src < kFewPaths;
+        const double degree = (double)g->m / g->n;
+        const bool light = std::ldexp(degree * degree * n_src, -(int)deep_share) < kFewPaths;
         if (bpc < xm::kFullBlocksPerCu || L.e_max == 1 || (g->n_hubs == 0 && light))
             bpc = std::min(bpc, xm::kRoomyBlocksPerCu);
         L.waves_per_cu = (uint32_t)std::max(1, bpc) * xm::kWavesPerBlock;

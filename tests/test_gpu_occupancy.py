@@ -17,18 +17,18 @@ def xa():
     return xa
 
 
-@pytest.mark.parametrize("n, deg, names, waves", [(3001, 4, "ffl,c4", 12), (300007, 4, "ffl,c4", 12),
-                                                  (466100, 24, "ffl", 12), (466000, 24, "c4", 12),
-                                                  (466100, 24, "c4", 24)])
-def test_graphs_without_long_lists(xa, n, deg, names, waves):
+@pytest.mark.parametrize("n, deg, names, share, waves", [
+    (3001, 4, "ffl,c4", 0, 12), (300007, 4, "ffl,c4", 0, 12), (466100, 24, "ffl", 0, 12), (466000, 24, "c4", 0, 12),
+    (466100, 24, "c4", 0, 24), (466100, 24, "c4", 1, 12)])
+def test_graphs_without_long_lists(xa, n, deg, names, share, waves):
     """Little to do: 12 waves per CU, whose kernel tests short lists against a bit map
     in LDS.  Plans of several levels with 2^28 or more 2-paths: 24."""
     g = xmgen.uniform_digraph(n, deg * n, 1)
     pats = [xmgen.named(p) for p in names.split(",")]
     G = xa.Graph(g)
     assert max(G.info()["max_out"], G.info()["max_in"]) <= 64
-    plans = [xa.Plan(p, graph=G) for p in pats]
-    print("[case]", n, deg, names, flush=True)
+    plans = [xa.Plan(p, graph=G, root_share=share) for p in pats]
+    print("[case]", n, deg, names, share, flush=True)
     assert xa.api.workspace_bytes(G, plans) == xa.api.workspace_bytes(G, plans, waves_per_cu=waves)
     assert xa.api.workspace_bytes(G, plans, waves_per_cu=12) != xa.api.workspace_bytes(G, plans, waves_per_cu=24)
     got = xa.count(G, plans)
