@@ -47,7 +47,9 @@ constexpr uint32_t kNapMax = 128;          // longest pause between two polls, i
 // serves ~70 accesses a us, so looks, donated tasks and waiters have to stay few.
 // A tenth of the roots of R-MAT 16 took, with ranges of 2^18 / 2^20 / 2^21 clocks
 // and 512 waiters, 730 / 60 / - ms, with 256 waiters and 2^21 40 ms, without
-// ranges 48 ms; all idle waves waiting with long pauses 51 ms.
+// ranges 48 ms; all idle waves waiting with long pauses 51 ms (while donors still
+// polled until the queue was empty; now 31 ms.  With 512 waiters now: a 6-vertex
+// pattern on 1/17 of R-MAT 14's roots 152 / 132 ms, stars on R-MAT 12 0.56 / 0.59).
 constexpr uint32_t kDonateClocks = 1u << 20;
 constexpr uint32_t kDonatePiece = 64;
 constexpr uint32_t kDonateWork = 1u << 21;
